@@ -77,6 +77,15 @@ static hipError_t launch_tile_batch(int stage, const RunDesc* runs, const int2* 
     return hipGetLastError();
 }
 
+int stage_slots(bool mixed)
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        ncu = 256;
+    return ncu * (mixed ? 3 : 2);
+}
+
 bool stage_tile_supported(int tx, int ty)
 {
     return (tx == 16 && ty == 15) || (tx == 32 && ty == 7) || (tx == 16 && ty == 16) || (tx == 32 && ty == 8) ||

@@ -524,22 +524,19 @@ int m2c_create(const m2c_config* cfg, m2c_ctx** out)
 
     // stage tiles: (tile_x, tile_y), else 16x15 (its 511 in-plane faces are
     // exactly two rounds of the block's 256 threads), 64x2 for quasi-1D
-    // grids.  Planes per block: tile_z,
-    // else the most of 32, 16 that still leaves at least 4096 blocks (16
-    // rounds of two blocks per CU: the prologue of a block's march and the
-    // re-read halo planes are amortised over more planes; 32 measured 1.5%
-    // faster than 16 on 384^3), otherwise 8.
+    // grids.  Planes per block: tile_z, else stage_planes.
     c->tx = cfg->tile_x ? cfg->tile_x : 16;
     c->ty = cfg->tile_y ? cfg->tile_y : 15;
     if (!cfg->tile_x && c->g.ny == 1) {
         c->tx = 64;
         c->ty = 2;
     }
-    if (cfg->tile_z) {
-        c->kz = cfg->tile_z;
-    } else {
+    c->kz = cfg->tile_z;
+    if (!c->kz) {
         const long long txy = (long long)((c->g.nx + c->tx - 1) / c->tx) * ((c->g.ny + c->ty - 1) / c->ty);
-        c->kz = txy * ((c->g.nz + 31) / 32) >= 4096 ? 32 : (txy * ((c->g.nz + 15) / 16) >= 4096 ? 16 : 8);
+        const int nz = c->g.nz;
+        c->kz = stage_planes([&](int kz) { return txy * ((nz + kz - 1) / kz); },
+                             stage_slots(cfg->precision == M2C_PREC_MIXED));
     }
     if (c->kz > c->g.nz) c->kz = c->g.nz;
     c->tiles[0] = (c->g.nx + c->tx - 1) / c->tx;
@@ -851,8 +848,9 @@ int m2c_autotune(m2c_ctx* c, int32_t steps, int32_t tile_out[3], float* ms_out)
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (!rc && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess))
         rc = set_err(c, M2C_ERR_DEVICE, "event create");
-    for (int ci = 0; ci < ncand; ++ci) {
-        const int* cand = cands[ci];
+    const int own[3] = {c->tx, c->ty, c->kz};          // the present tile competes too
+    for (int ci = -1; ci < ncand; ++ci) {
+        const int* cand = ci < 0 ? own : cands[ci];
         if (rc) break;
         set_tile(cand[0], cand[1], cand[2]);
         if ((rc = restore()) || (rc = run_steps(c, 1, 0.0, nullptr)) || (rc = restore())) break;

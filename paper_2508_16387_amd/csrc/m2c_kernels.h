@@ -71,6 +71,32 @@ struct PhaseArgs {
 };
 
 bool stage_tile_supported(int tx, int ty);
+// Stage blocks resident on the chip at once: two per CU (FP64) or three
+// (mixed), from the stage kernels' registers.
+int stage_slots(bool mixed);
+// Planes per stage block, from the number of blocks at a given number of
+// planes (blocks: int -> long long).  Three regimes:
+//   at least 4096 blocks with 32 or 16 planes (16 rounds of two blocks per
+//     CU): that many, so that the prologue of a block's march and the
+//     re-read halo planes are amortised (32 measured 1.5% faster than 16 on
+//     384^3);
+//   grids whose blocks of fewer than 8 planes all fit on the chip at once:
+//     the fewest planes that still fit.  There the launch lasts as long as
+//     one block's march, so fewer planes are a shorter launch until the
+//     blocks no longer run side by side (per stage launch, 8 planes -> this
+//     rule: 32^3 47 -> 14 us, 50x43x37 54 -> 18 us, 64^3 52 -> 31 us, mixed
+//     96^3 71 -> 62 us; one plane fewer than fits: 64^3 36 us, 80^3 58
+//     against 46 us);
+//   otherwise 8 (128^3: 128 us; 4, 6, 10 and 16 planes: 143, 142, 131, 149).
+template <class Blocks>
+int stage_planes(Blocks blocks, int slots)
+{
+    if (blocks(32) >= 4096) return 32;
+    if (blocks(16) >= 4096) return 16;
+    for (int kz = 1; kz < 8; ++kz)
+        if (blocks(kz) <= slots) return kz;
+    return 8;
+}
 // stage: kind 1 (first), 2 (last, blended), 3 (middle of RK3), 4 (forward
 // Euler); the batched kernel has kinds 1 and 2 (TVD-RK2)
 hipError_t launch_stage(int stage, bool mixed, int tx, int ty, const StageArgs& a, hipStream_t s);

@@ -477,9 +477,9 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
                 if (!live) continue;
                 it = 0;
                 for (int k = 0; k < 4; ++k) o[k] = __builtin_nan("");
-                if (ok) it = eos::pair_solve<S0, S1>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
+                if (ok) it = eos::pair_solve<S0, S1, 8>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
             } else {
-                it = eos::solve_pair<S0, S1>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
+                it = eos::solve_pair<S0, S1, 8>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
             }
             out[0] = o[0];
             out[1] = flip ? -o[1] : o[1];

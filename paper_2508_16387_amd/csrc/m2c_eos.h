@@ -259,8 +259,17 @@ struct Wave {
 // One classical RK4 step of the isentrope over y = ln(p - floor), from
 // (y, s, f) to y + h: ds/dy = (p - floor)/(rho c^2), df/dy = c ds/dy.
 // False where c^2 <= 0 (outside the convex part of the EOS).
+// q0, qh, q1: exp(y), exp(y + h/2), exp(y + h); rho0 = rho_K exp(s) and
+// eta0 = 1 - rho_0/rho0 of the start.
+// The step is one serial chain of four stages (each an exponential, two or
+// three reciprocals and the reference curve), and a solve near cavitation
+// takes hundreds to 2500 of them while most of the chip has nothing left to
+// do, so only what the chain needs is on it: the exponentials of y come from
+// outside, and the branch look-ahead below ends early away from a branch
+// point.
 template <int S = FAM_ALL>
-M2C_HDI bool rk4_y(const EosK& m, const Side& K, double y, double h, double& s, double& f)
+M2C_HDI bool rk4_y(const EosK& m, const Side& K, double h, double q0, double qh, double q1, double rho0, double eta0,
+                   double& s, double& f)
 {
     double ks[4], kf[4];
     // every stage on one Mie-Grueneisen branch: a step never spans a branch
@@ -268,25 +277,96 @@ M2C_HDI bool rk4_y(const EosK& m, const Side& K, double y, double h, double& s, 
     // overshoot it, and a step may start on one.  The branch is the one a
     // quarter step ahead (s moves with y, ds/dy > 0).
     int br = 0;
+    double c2 = 0.0;
+    bool have = false;                   // c2 is that of the first stage
     if (fam_of<S>(m) == M2C_EOS_MG) {
-        const double rho0 = K.rho * exp(s), q0 = exp(y);
-        const double c20 = eos_c2<S>(m, rcp(rho0), K.fl + q0);
-        if (!(c20 > 0.0)) return false;
-        const double probe = s + 0.25 * h * q0 * rcp(rho0 * c20);
-        br = mg_branch(m, 1.0 - m.k[0] * rcp(K.rho * exp(probe)));
+        const int b0 = mg_branch(m, eta0);
+        c2 = eos_c2_on<S>(m, rcp(rho0), K.fl + q0, b0);
+        if (!(c2 > 0.0)) return false;
+        const double ahead = 0.25 * h * q0 * rcp(rho0 * c2);
+        // (eta moves by less than (1 - eta) (exp|ahead| - 1))
+        if (eta0 > 1e-9 && fabs(ahead) < 0.25 * eta0) br = 0;
+        else br = mg_branch(m, 1.0 - m.k[0] * rcp(K.rho * exp(s + ahead)));
+        have = br == b0;
     }
+    // (the four stages in straight-line code: as a loop they kept their
+    // slopes in LDS; a stage outside the convex part is noticed at the end)
+    bool ok = true;
+#pragma unroll
     for (int j = 0; j < 4; ++j) {
         const double a = j == 0 ? 0.0 : (j == 3 ? h : 0.5 * h);
-        const double ss = j == 0 ? s : s + a * ks[j - 1];
-        const double q = exp(y + a), rho = K.rho * exp(ss);
-        const double c2 = eos_c2_on<S>(m, rcp(rho), K.fl + q, br);
-        if (!(c2 > 0.0) || !isfinite(c2)) return false;
+        const double q = j == 0 ? q0 : (j == 3 ? q1 : qh);
+        const double rho = j == 0 ? rho0 : K.rho * exp(s + a * ks[j - 1]);
+        if (!(j == 0 && have)) c2 = eos_c2_on<S>(m, rcp(rho), K.fl + q, br);
+        ok = ok && c2 > 0.0 && isfinite(c2);
         ks[j] = q * rcp(rho * c2);
         kf[j] = ks[j] * sqrt(c2);
     }
+    if (!ok) return false;
     s += h * (ks[0] + 2.0 * ks[1] + 2.0 * ks[2] + ks[3]) * (1.0 / 6.0);
     f += h * (kf[0] + 2.0 * kf[1] + 2.0 * kf[2] + kf[3]) * (1.0 / 6.0);
     return isfinite(s) && isfinite(f);
+}
+
+// The walk's steps while they stay inside the Mie-Grueneisen compression
+// branch, from K towards y = Y; stops there, or before a step that reaches a
+// branch point or leaves the convex part (the caller takes that step).  q0
+// is kept equal to exp(K.y).
+// A solve near cavitation takes up to 2500 of these steps, one after
+// another, in a launch whose other wavefronts have long finished, so the
+// chain of one step sets the time: the step is straight-line code with one
+// exit test, and the next step's length and exponentials of y, which do not
+// depend on it, are computed beside it.  2^18 problems of eight material
+// pairs: 7.0 -> 3.0 ms, all of it the longest chain (2.8 -> 1.2 us a step);
+// 2^18 of copper against tantalum 21 -> 10 ms.
+template <int S>
+M2C_HDI void march_compressed(const EosK& m, Side& K, double Y, double hmax, double kink0, double kink1, double& q0)
+{
+    double y = K.y, s = K.s, f = K.f;
+    double rem = Y - y;
+    int n = (int)ceil(fabs(rem) / hmax);
+    double h = rem / (double)n;
+    double qh = exp(y + 0.5 * h), q1 = exp(y + h);
+    for (int guard = 0; guard < 100000; ++guard) {
+        // the step (rk4_y on branch 0)
+        const double rho0 = K.rho * exp(s), v0 = rcp(rho0), eta0 = 1.0 - m.k[0] * v0;
+        double ks[4], kf[4], ahead = 0.0;
+        bool ok = eta0 > 1e-6;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const double a = j == 0 ? 0.0 : (j == 3 ? h : 0.5 * h);
+            const double q = j == 0 ? q0 : (j == 3 ? q1 : qh);
+            const double rho = j == 0 ? rho0 : K.rho * exp(s + a * ks[j - 1]);
+            const double c2 = eos_c2_on<S>(m, j == 0 ? v0 : rcp(rho), K.fl + q, 0);
+            ok = ok && c2 > 0.0 && isfinite(c2);
+            ks[j] = q * rcp(rho * c2);
+            kf[j] = ks[j] * sqrt(c2);
+            if (j == 0) ahead = 0.25 * h * ks[0];
+        }
+        double s1 = s, f1 = f;
+        s1 += h * (ks[0] + 2.0 * ks[1] + 2.0 * ks[2] + ks[3]) * (1.0 / 6.0);
+        f1 += h * (kf[0] + 2.0 * kf[1] + 2.0 * kf[2] + kf[3]) * (1.0 / 6.0);
+        ok = ok && isfinite(s1) && isfinite(f1) && fabs(ahead) < 0.25 * eta0 &&
+             !((s - kink0) * (s1 - kink0) < 0.0) && !((s - kink1) * (s1 - kink1) < 0.0);
+        // what the next step needs of y
+        const double y1 = n == 1 ? Y : y + h, rem1 = Y - y1;
+        const int n1 = (int)ceil(fabs(rem1) / hmax);
+        const double h1 = rem1 / (double)n1;
+        const double qh1 = exp(y1 + 0.5 * h1), q11 = exp(y1 + h1);
+        if (!ok) break;
+        y = y1;
+        s = s1;
+        f = f1;
+        q0 = q1;
+        if (rem1 == 0.0) break;
+        n = n1;
+        h = h1;
+        qh = qh1;
+        q1 = q11;
+    }
+    K.y = y;
+    K.s = s;
+    K.f = f;
 }
 
 // Walk the side's isentrope from its current point to y = Y in steps of at
@@ -297,26 +377,38 @@ M2C_HDI bool rk4_y(const EosK& m, const Side& K, double y, double h, double& s, 
 template <int S = FAM_ALL>
 M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
 {
-    double kink[2] = {INFINITY, INFINITY};
+    double kink0 = INFINITY, kink1 = INFINITY;        // s of the branch points ahead
     if (fam_of<S>(m) == M2C_EOS_MG) {
-        kink[0] = log(m.k[0] / K.rho);
-        kink[1] = log(m.k[0] / ((1.0 - m.k[4]) * K.rho));
+        kink0 = log(m.k[0] / K.rho);
+        kink1 = log(m.k[0] / ((1.0 - m.k[4]) * K.rho));
     }
+    double q0 = exp(K.y);                // kept equal to exp(K.y)
     for (int guard = 0; guard < 100000; ++guard) {
-        const double rem = Y - K.y;
+        double rem = Y - K.y;
         if (rem == 0.0) return true;
-        if (fam_of<S>(m) == M2C_EOS_MG) {
+        double rho0 = K.rho * exp(K.s), eta0 = 1.0 - m.k[0] * rcp(rho0);
+        if (fam_of<S>(m) == M2C_EOS_MG && eta0 > 1e-6) {
+            march_compressed<S>(m, K, Y, hmax, kink0, kink1, q0);
+            rem = Y - K.y;
+            if (rem == 0.0) return true;
+            rho0 = K.rho * exp(K.s);
+            eta0 = 1.0 - m.k[0] * rcp(rho0);
+        }
+        if (fam_of<S>(m) == M2C_EOS_MG && !(eta0 > 1e-6)) {
+            // (a point further inside the compression branch than the
+            // look-ahead below can reach is on none of the two others)
             // below eta_min the isentrope is known in closed form: there
             // c^2 = rho_0 Gamma_0 (p - p_min) v^2, so ds/dy = rho/(rho_0
             // Gamma_0), i.e. exp(-s) falls linearly in y, and df/dy =
             // sqrt((p - p_min)/(rho_0 Gamma_0))
             const double dir = rem > 0.0 ? 1.0 : -1.0;
-            if (mg_branch(m, 1.0 - m.k[0] / (K.rho * exp(K.s + dir * 1e-10))) == 2) {
+            const int bahead = mg_branch(m, 1.0 - m.k[0] / (K.rho * exp(K.s + dir * 1e-10)));
+            if (bahead == 2) {
                 const double a = K.rho * m.k[8];
                 double yend = Y;
                 bool to_kink = false;
-                if (dir > 0.0 && isfinite(kink[1])) {
-                    const double yk = K.y + (exp(-K.s) - exp(-kink[1])) / a;
+                if (dir > 0.0 && isfinite(kink1)) {
+                    const double yk = K.y + (exp(-K.s) - exp(-kink1)) / a;
                     if (yk < Y) {
                         yend = yk;
                         to_kink = true;
@@ -325,12 +417,13 @@ M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
                 const double em = exp(-K.s) - a * (yend - K.y);
                 if (!(em > 0.0)) return false;
                 K.f += 2.0 * sqrt(m.k[8]) * (exp(0.5 * yend) - exp(0.5 * K.y));
-                K.s = to_kink ? kink[1] + 1e-12 * (1.0 + fabs(kink[1])) : -log(em);
+                K.s = to_kink ? kink1 + 1e-12 * (1.0 + fabs(kink1)) : -log(em);
                 K.y = yend;
-                if (to_kink) kink[1] = INFINITY;
+                q0 = exp(K.y);
+                if (to_kink) kink1 = INFINITY;
                 continue;
             }
-            if (mg_branch(m, 1.0 - m.k[0] / (K.rho * exp(K.s + dir * 1e-10))) == 1) {
+            if (bahead == 1) {
                 // small tension: along the isentrope e - e_R(eta) decays as
                 // exp(-rho_0 Gamma_0 v) (de = -p dv with p_R = K_0 eta, e_R
                 // quadratic), so p(v) = K_0 (1 - rho_0 v) + (p_a - K_0 eta_a)
@@ -342,7 +435,7 @@ M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
                 const double ga = (K.fl + exp(K.y)) - K0 * (1.0 - r0 * va);     // rho_0 Gamma_0 (e - e_R)
                 auto P = [&](double v) { return K0 * (1.0 - r0 * v) + ga * exp(-G * (v - va)); };
                 auto mdP = [&](double v) { return K0 * r0 + G * ga * exp(-G * (v - va)); };   // -dp/dv
-                const int j = dir < 0.0 ? 1 : 0;
+                const double kj = dir < 0.0 ? kink1 : kink0;
                 const double vk = dir < 0.0 ? (1.0 - m.k[4]) / r0 : 1.0 / r0;
                 const double pt = K.fl + exp(Y), pk = P(vk);
                 const bool to_kink = dir < 0.0 ? pt <= pk : pt >= pk;
@@ -390,34 +483,38 @@ M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
                     K.f -= I;
                 }
                 if (to_kink) {
-                    K.s = kink[j] + (dir < 0.0 ? -1e-12 : 1e-12) * (1.0 + fabs(kink[j]));
-                    if (!isfinite(kink[j])) K.s = log(K.v / vk);
+                    K.s = kj + (dir < 0.0 ? -1e-12 : 1e-12) * (1.0 + fabs(kj));
+                    if (!isfinite(kj)) K.s = log(K.v / vk);
                     K.y = log(pk - K.fl);
-                    kink[j] = INFINITY;
+                    if (dir < 0.0) kink1 = INFINITY;
+                    else kink0 = INFINITY;
                 } else {
                     K.s = log(K.v / v);
                     K.y = Y;
                 }
+                q0 = exp(K.y);
                 continue;
             }
         }
         const int n = (int)ceil(fabs(rem) / hmax);
         const double h = rem / (double)n;
         double s = K.s, f = K.f;
-        if (!rk4_y<S>(m, K, K.y, h, s, f)) return false;
+        const double q1 = exp(K.y + h);
+        if (!rk4_y<S>(m, K, h, q0, exp(K.y + 0.5 * h), q1, rho0, eta0, s, f)) return false;
         int crossed = -1;
-        for (int j = 0; j < 2; ++j)
-            if ((K.s - kink[j]) * (s - kink[j]) < 0.0) crossed = j;
+        if ((K.s - kink0) * (s - kink0) < 0.0) crossed = 0;
+        if ((K.s - kink1) * (s - kink1) < 0.0) crossed = 1;
         if (crossed < 0) {
             K.y = n == 1 ? Y : K.y + h;
             K.s = s;
             K.f = f;
+            q0 = q1;                         // (read again only where K.y is y + h)
             continue;
         }
         // shorten the step so that it ends on the branch point: root of
         // g(hk) = s(hk) - s_kink on [0, h] by the Illinois variant of
         // regula falsi (c^2, and with it the slope of g, may jump there)
-        const double sk = kink[crossed];
+        const double sk = crossed ? kink1 : kink0;
         double a = 0.0, ga = K.s - sk, b = h, gb = s - sk;
         double hk = b, sk_got = s, fk_got = f;
         int side = 0;
@@ -425,7 +522,7 @@ M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
             hk = (a * gb - b * ga) / (gb - ga);
             sk_got = K.s;
             fk_got = K.f;
-            if (!rk4_y<S>(m, K, K.y, hk, sk_got, fk_got)) return false;
+            if (!rk4_y<S>(m, K, hk, q0, exp(K.y + 0.5 * hk), exp(K.y + hk), rho0, eta0, sk_got, fk_got)) return false;
             const double g = sk_got - sk;
             if (fabs(g) <= 1e-14 * (1.0 + fabs(sk)) || fabs(b - a) <= 1e-15 * fabs(h)) break;
             if ((g < 0.0) == (gb < 0.0)) {
@@ -445,9 +542,10 @@ M2C_HDI bool walk(const EosK& m, Side& K, double Y, double hmax)
         // at eta_min); the offset is far below the step error
         const double dir = s > K.s ? 1.0 : -1.0;
         K.y += hk;
+        q0 = exp(K.y);
         K.s = sk_got + dir * 1e-12 * (1.0 + fabs(sk));
         K.f = fk_got;
-        kink[crossed] = INFINITY;            // passed
+        (crossed ? kink1 : kink0) = INFINITY;         // passed
     }
     return false;
 }
@@ -468,6 +566,7 @@ M2C_HD inline void jwl_ps(const EosK& m, double C, double v, double& ps, double&
 // most 0.1 in ln v; where both exponentials are below e^-40 of their
 // amplitude the integrand is the power law sqrt((1 + omega) C) v^-(1 + omega/2)
 // and the rest is integrated in closed form.  False where -p_s' <= 0.
+template <int NB>
 M2C_HDI bool jwl_quad(const EosK& m, double C, double v0, double v1, double& I)
 {
     const double gx[4] = {0.1834346424956498, 0.5255324099163290, 0.7966664774136267, 0.9602898564975363};
@@ -488,14 +587,29 @@ M2C_HDI bool jwl_quad(const EosK& m, double C, double v0, double v1, double& I)
         const double hu = n > 0 ? (u1 - u0) / n : 0.0;
         for (int i = 0; i < n; ++i) {
             const double um = u0 + (i + 0.5) * hu;
+            // the nodes are independent: NB of them are evaluated together, so
+            // that their exponentials and logarithms overlap, and summed in
+            // order (NB = 8 where a kernel runs one wave per SIMD, so that
+            // nothing else covers their latency; 1 in the point solvers of
+            // one family pair, which run two waves per SIMD and would spill)
             double sum = 0.0;
-            for (int j = 0; j < 8; ++j) {
-                const double u = um + 0.5 * hu * (j < 4 ? -gx[j] : gx[j - 4]);
-                const double v = exp(u);
-                double ps, dps;
-                jwl_ps(m, C, v, ps, dps);
-                if (!(dps < 0.0)) return false;
-                sum += gw[j & 3] * sqrt(-dps) * v;
+#pragma unroll 1
+            for (int j0 = 0; j0 < 8; j0 += NB) {
+                double t[NB], vj[NB];
+                bool convex = true;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const int j = j0 + b;
+                    const double u = um + 0.5 * hu * (j < 4 ? -gx[j & 3] : gx[j & 3]);
+                    vj[b] = exp(u);
+                    double ps, dps;
+                    jwl_ps(m, C, vj[b], ps, dps);
+                    convex = convex && dps < 0.0;
+                    t[b] = gw[j & 3] * sqrt(-dps);
+                }
+                if (!convex) return false;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) sum += t[b] * vj[b];
             }
             acc += 0.5 * hu * sum;
         }
@@ -506,6 +620,7 @@ M2C_HDI bool jwl_quad(const EosK& m, double C, double v0, double v1, double& I)
 
 // f_K(p) for p <= p_K on a JWL side: v* from p_s(v*) = p by safeguarded
 // Newton in ln v, f continued from the last point of this isentrope.
+template <int NB>
 M2C_HDI bool jwl_rarefaction(const EosK& m, Side& K, double p, Wave& w)
 {
     const double C = K.jC;
@@ -541,7 +656,7 @@ M2C_HDI bool jwl_rarefaction(const EosK& m, Side& K, double p, Wave& w)
     if (!(dps < 0.0)) return false;
     double I;
     const double vlast = K.v * exp(-K.s);
-    if (!jwl_quad(m, C, vlast, v, I)) return false;
+    if (!jwl_quad<NB>(m, C, vlast, v, I)) return false;
     K.f -= I;
     K.s = log(K.v / v);
     w.f = K.f;
@@ -551,7 +666,7 @@ M2C_HDI bool jwl_rarefaction(const EosK& m, Side& K, double p, Wave& w)
 }
 
 // f_K(p) for p <= p_K: the isentrope walked to y = ln(p - floor).
-template <int S = FAM_ALL>
+template <int S = FAM_ALL, int NB = 1>
 M2C_HDI bool rarefaction(const EosK& m, Side& K, double p, double hmax, Wave& w)
 {
     if (fam_of<S>(m) == M2C_EOS_JWL) {
@@ -561,7 +676,7 @@ M2C_HDI bool rarefaction(const EosK& m, Side& K, double p, double hmax, Wave& w)
             w.df = 1.0 / (K.rho * K.c);
             return true;
         }
-        return jwl_rarefaction(m, K, p, w);
+        return jwl_rarefaction<NB>(m, K, p, w);
     }
     if (fam_of<S>(m) == M2C_EOS_NASG) {
         // closed form: along the isentrope (p + p_c)(v - b)^gamma is
@@ -652,10 +767,10 @@ M2C_HDI bool shock(const EosK& m, Side& K, double p, Wave& w)
     return true;
 }
 
-template <int S = FAM_ALL>
+template <int S = FAM_ALL, int NB = 1>
 M2C_HDI bool wave(const EosK& m, Side& K, double p, double hmax, Wave& w)
 {
-    return p > K.p ? shock<S>(m, K, p, w) : rarefaction<S>(m, K, p, hmax, w);
+    return p > K.p ? shock<S>(m, K, p, w) : rarefaction<S, NB>(m, K, p, hmax, w);
 }
 
 M2C_HD inline double floor_margin(const Side& K)
@@ -735,8 +850,9 @@ M2C_HDI bool pair_init(const EosK& mL, const EosK& mR, const double* q, Pair& P)
 // the tangent there predicts a smaller |F| at the acoustic start.  F is
 // increasing in p, so Newton converges from either start, and the answer
 // does not depend on the candidate beyond the stopping tolerance.  *used
-// (nullable): the candidate was the start.
-template <int SL = FAM_ALL, int SR = FAM_ALL>
+// (nullable): the candidate was the start.  NB: quadrature nodes evaluated
+// together (jwl_quad).
+template <int SL = FAM_ALL, int SR = FAM_ALL, int NB = 1>
 M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int maxit, double hmax,
                              double guess, double* res, bool* used = nullptr)
 {
@@ -751,7 +867,7 @@ M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int
     Wave wl, wr;
     if (guess > pfl && isfinite(guess)) {
         Wave a, b;
-        if (wave<SL>(mL, L, guess, hmax, a) && wave<SR>(mR, R, guess, hmax, b)) {
+        if (wave<SL, NB>(mL, L, guess, hmax, a) && wave<SR, NB>(mR, R, guess, hmax, b)) {
             const double F = a.f + b.f + du, dF = a.df + b.df;
             if (F < 0.0) lo = guess; else hi = guess;
             if (fabs(F) <= fabs(F + dF * (p - guess))) {
@@ -766,7 +882,7 @@ M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int
     }
     int its;
     for (its = 1; its <= maxit; ++its) {
-        if (!(first && its == 1) && (!wave<SL>(mL, L, p, hmax, wl) || !wave<SR>(mR, R, p, hmax, wr))) {
+        if (!(first && its == 1) && (!wave<SL, NB>(mL, L, p, hmax, wl) || !wave<SR, NB>(mR, R, p, hmax, wr))) {
             // p lies below where an isentrope ends (c^2 reaches zero
             // before the floor): it bounds the bracket from below
             lo = fmax(lo, p);
@@ -797,7 +913,7 @@ M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int
                 // there a star state above the floor at all?
                 floor_checked = true;
                 Wave a, b;
-                if (!wave<SL>(mL, L, pfl, hmax, a) || !wave<SR>(mR, R, pfl, hmax, b)) break;
+                if (!wave<SL, NB>(mL, L, pfl, hmax, a) || !wave<SR, NB>(mR, R, pfl, hmax, b)) break;
                 if (a.f + b.f + du > 0.0) break;          // cavitation
             }
             pn = isinf(hi) ? p + fmax(p - pfl, fabs(p) + 1.0) : bisect(lo, hi, base);
@@ -805,7 +921,7 @@ M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int
         }
         p = pn;
     }
-    if (conv && wave<SL>(mL, L, p, hmax, wl) && wave<SR>(mR, R, p, hmax, wr)) {
+    if (conv && wave<SL, NB>(mL, L, p, hmax, wl) && wave<SR, NB>(mR, R, p, hmax, wr)) {
         res[0] = p;
         res[1] = 0.5 * (uL - wl.f + uR + wr.f);
         res[2] = wl.rho;
@@ -818,7 +934,7 @@ M2C_HDI int pair_solve(const EosK& mL, const EosK& mR, Pair& P, double rtol, int
 // One problem: q = (rho_L, u_L, p_L, rho_R, u_R, p_R) of materials mL, mR
 // from the acoustic start; res and the return value as for pair_solve (0
 // also for an inadmissible input).
-template <int SL = FAM_ALL, int SR = FAM_ALL>
+template <int SL = FAM_ALL, int SR = FAM_ALL, int NB = 1>
 M2C_HDI int solve_pair(const EosK& mL, const EosK& mR, const double* q, double rtol, int maxit, double hmax,
                              double* res)
 {
@@ -827,7 +943,7 @@ M2C_HDI int solve_pair(const EosK& mL, const EosK& mR, const double* q, double r
         for (int k = 0; k < 4; ++k) res[k] = __builtin_nan("");
         return 0;
     }
-    return pair_solve<SL, SR>(mL, mR, P, rtol, maxit, hmax, __builtin_nan(""), res);
+    return pair_solve<SL, SR, NB>(mL, mR, P, rtol, maxit, hmax, __builtin_nan(""), res);
 }
 
 // The same for materials ml, mr of a table (0 for an index out of range).

@@ -11,7 +11,7 @@
 // Layer 2: Z2^T (64x16) = W2 (64x64) H1^T                 -> 16 MFMA
 // Layer 3: y (16) = w3 . H2^T + b3                         -> lane sums + shuffles
 // Backward (training): dW2 = dZ2^T H1 and dW1 = dZ1^T X accumulate over the
-// wave's chunks in MFMA accumulators (the transposes go through LDS),
+// block's samples in MFMA accumulators (the transposes go through LDS),
 // dH1^T = W2^T dZ2^T reuses dZ2^T in place as the B operand.
 #include "m2c_device.h"
 #include "m2c_internal.h"
@@ -31,33 +31,26 @@ __device__ __forceinline__ float group16_sum(float v)
     return v;
 }
 
-// Forward pass of 16 samples held by one wave.  xb: this lane's B operand of
-// layer 1 (features 4g..4g+3 of sample l%16, zero for g >= 2).  Produces the
-// hidden activations in D layout (h1[c][e] = H1^T[16c+4g+e][l%16], same for
-// h2) and y of sample l%16 in every lane of that sample.
+// Forward pass of 16 samples held by one wave, the weights in registers.
+// xb: this lane's B operand of layer 1 (features 4g..4g+3 of sample l%16,
+// zero for g >= 2).  Produces the hidden activations in D layout (h1[c][e] =
+// H1^T[16c+4g+e][l%16], same for h2) and y of sample l%16 in every lane of
+// that sample.
 struct Fwd {
     float h1[4][4], h2[4][4];
     float y;
 };
 
-__device__ __forceinline__ void mlp_fwd16(const float* __restrict__ P, const uint16_t* __restrict__ wbf, bf16x4 xb,
-                                          Fwd& f)
+__device__ __forceinline__ void mlp_fwd16(const MlpRegs& w, bf16x4 xb, Fwd& f)
 {
-    const int l = threadIdx.x & 63, g = l >> 4, r = l & 15;
     // layer 1
     bf16x4 hb[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        bf16x4 a;
+        const f32x4 z = mfma(w.a1[t], xb, f32x4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int k = 4 * g + e;
-            a[e] = k < MLP_IN ? (short)wbf[MLP_OFF_W1 + (16 * t + r) * MLP_IN + k] : (short)0;
-        }
-        f32x4 z = mfma(a, xb, f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float h = tanhf(z[e] + P[MLP_OFF_B1 + 16 * t + 4 * g + e]);
+            const float h = tanhf(z[e] + w.b1[t][e]);
             f.h1[t][e] = h;
             hb[t][e] = to_bf16(h);
         }
@@ -68,33 +61,35 @@ __device__ __forceinline__ void mlp_fwd16(const float* __restrict__ P, const uin
     for (int u = 0; u < 4; ++u) {
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            bf16x4 a;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] = (short)wbf[512 + (16 * u + r) * MLP_H + 16 * c + 4 * g + e];
-            z = mfma(a, hb[c], z);
-        }
+        for (int c = 0; c < 4; ++c) z = mfma(w.a2[u][c], hb[c], z);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int h = 16 * u + 4 * g + e;
-            const float v = tanhf(z[e] + P[MLP_OFF_B2 + h]);
+            const float v = tanhf(z[e] + w.b2[u][e]);
             f.h2[u][e] = v;
-            part += P[MLP_OFF_W3 + h] * v;
+            part += w.w3[u][e] * v;
         }
     }
     // layer 3: sum the four lane groups of each sample
     part += __shfl_xor(part, 16);
     part += __shfl_xor(part, 32);
-    f.y = part + P[MLP_OFF_B3];
+    f.y = part + w.b3;
 }
 
-// This lane's layer-1 B operand from the 8 features of its sample.
-__device__ __forceinline__ bf16x4 xb_of(const float x[8])
+// This lane's features 4g..4g+3 of sample i (zeros for g >= 2 and beyond
+// the samples), and the layer-1 B operand they make.
+__device__ __forceinline__ void load_features(const float* __restrict__ X, long long n, long long i, bool live,
+                                              float x[4])
 {
     const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = live && g < 2 ? X[(4 * g + e) * n + i] : 0.f;
+}
+
+__device__ __forceinline__ bf16x4 xb_of(const float x[4])
+{
     bf16x4 b;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) b[e] = g < 2 ? to_bf16(x[4 * g + e]) : (short)0;
+    for (int e = 0; e < 4; ++e) b[e] = to_bf16(x[e]);
     return b;
 }
 
@@ -136,13 +131,15 @@ __global__ __launch_bounds__(256) void k_mlp_forward(long long n, const float* _
     const int l = threadIdx.x & 63, r = l & 15;
     const long long wave = (blockIdx.x * (long long)blockDim.x + threadIdx.x) >> 6;
     const long long nw = ((long long)gridDim.x * blockDim.x) >> 6;
+    if (wave * 16 >= n) return;                                   // wave-uniform
+    MlpRegs w;
+    mlp_load_regs(P, wbf, w);
     for (long long c = wave; c * 16 < n; c += nw) {
         const long long i = c * 16 + r;
-        float x[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = i < n ? X[k * n + i] : 0.f;
+        float x[4];
+        load_features(X, n, i, i < n, x);
         Fwd f;
-        mlp_fwd16(P, wbf, xb_of(x), f);
+        mlp_fwd16(w, xb_of(x), f);
         if (l < 16 && i < n) y[i] = f.y;
     }
 }
@@ -150,7 +147,7 @@ __global__ __launch_bounds__(256) void k_mlp_forward(long long n, const float* _
 hipError_t launch_mlp_forward(long long n, const float* X, const MlpDev& m, float* y, hipStream_t s)
 {
     long long nb = (n + 63) / 64;               // 4 waves x 16 samples per block
-    if (nb > 8192) nb = 8192;
+    if (nb > 1536) nb = 1536;                  // two rounds of the resident blocks, so that the weights are loaded rarely
     if (nb < 1) nb = 1;
     hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)nb), dim3(256), 0, s, n, X, m.master, m.wbf, y);
     return hipGetLastError();
@@ -158,99 +155,99 @@ hipError_t launch_mlp_forward(long long n, const float* X, const MlpDev& m, floa
 
 // ---------------------------------------------------------------------------
 // Gradient of the mean squared error over samples [i0, i0 + cnt) of a
-// minibatch of size B, accumulated (atomically) into grad[MLP_NPARAM]; the
-// sum of squared errors goes to *sse.  One wave per CHUNKS x 16 samples.
-constexpr int GRAD_CHUNKS = 4;
+// minibatch of size B.  A block of four waves takes 64 samples at a time,
+// wave w the 16-sample chunk w of the forward pass and of dH1^T = W2^T dZ2^T;
+// the operands of the two weight gradients then go through LDS, and wave w
+// forms rows 16w..16w+15 of dW2 and dW1 over all 64 samples, so that no sum
+// over waves is left for them.  Each block writes its partial gradient (and
+// sum of squared errors) to part[block][GRAD_STRIDE]; k_adam / k_grad_sum
+// add the blocks up in a fixed order.
+//
+// What bounds it: a minibatch is a few thousand samples, so the kernel is one
+// chain of latencies (weights, two layers of tanh, transposes) on a fraction
+// of the chip.  Before, one wave per 64 samples walked four such chains,
+// loaded its weights two bytes at a time and added 4801 values per wave
+// atomically: 46 us for 4096 samples; now 14 us, of which the 32 tanh of a lane are a third.
+constexpr int GRAD_SAMPLES = 64;                   // per block and pass
+constexpr int GRAD_PITCH = GRAD_SAMPLES + 4;       // LDS row pitch: 16 rows, 8-byte reads, no bank twice
+static_assert(GRAD_SSE == MLP_NPARAM && GRAD_STRIDE >= GRAD_SSE + 1, "gradient partial layout");
 
-__global__ __launch_bounds__(64) void k_mlp_grad(long long i0, long long cnt, long long ntot, float invB,
-                                                 const float* __restrict__ X, const float* __restrict__ T,
-                                                 const float* __restrict__ P, const uint16_t* __restrict__ wbf,
-                                                 float* __restrict__ grad, float* __restrict__ sse)
+__global__ __launch_bounds__(256) void k_mlp_grad(long long i0, long long cnt, long long ntot, float invB,
+                                                  const float* __restrict__ X, const float* __restrict__ T,
+                                                  const float* __restrict__ P, const uint16_t* __restrict__ wbf,
+                                                  float* __restrict__ part)
 {
-    __shared__ short sA[64 * 16];      // dZ2^T or dZ1^T as [hidden][sample]
-    __shared__ short sB[64 * 16];      // H1^T as [hidden][sample]
-    __shared__ short sX[16 * 16];      // X as [sample][feature] (features 8..15 zero)
-    const int l = threadIdx.x, g = l >> 4, r = l & 15;
-    f32x4 dW2[4][4], dW1[4];
+    __shared__ __align__(8) short sA[64 * GRAD_PITCH];      // dZ2^T, then dZ1^T, as [hidden][sample]
+    __shared__ __align__(8) short sB[64 * GRAD_PITCH];      // H1^T as [hidden][sample]
+    __shared__ __align__(8) short sWT[64 * GRAD_PITCH];     // W2^T as [hidden 1][hidden 2]
+    __shared__ __align__(8) short sX[MLP_IN * GRAD_PITCH];  // X as [feature][sample]
+    __shared__ float sSum[4][3 * 64 + 2];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, r = l & 15;
+    MlpRegs net;
+    mlp_load_regs(P, wbf, net);
+    {
+        // thread t: row t/4 of W2, 16 columns from 16 (t%4)
+        const int row = threadIdx.x >> 2, c0 = 16 * (threadIdx.x & 3);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        dW1[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < 16; c += 4) {
+            const bf16x4 v = ld_bf16x4(wbf + 512 + row * MLP_H + c0 + c);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) dW2[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < 4; ++e) sWT[(c0 + c + e) * GRAD_PITCH + row] = v[e];
+        }
     }
+    f32x4 dW2[4], dW1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) dW2[v] = f32x4{0.f, 0.f, 0.f, 0.f};
     float gw3[4][4] = {}, gb2[4][4] = {}, gb1[4][4] = {};
     float gb3 = 0.f, err2 = 0.f;
-    const long long base = i0 + (long long)blockIdx.x * GRAD_CHUNKS * 16;
-    for (int ch = 0; ch < GRAD_CHUNKS; ++ch) {
-        const long long j0 = base + ch * 16;
-        if (j0 >= i0 + cnt) break;
-        const long long i = j0 + r;
+    const short* const row16 = sA + (16 * w + r) * GRAD_PITCH + 4 * g;
+    for (long long s0 = (long long)blockIdx.x * GRAD_SAMPLES; s0 < cnt; s0 += (long long)gridDim.x * GRAD_SAMPLES) {
+        const long long i = i0 + s0 + 16 * w + r;
         const bool live = i < i0 + cnt;
-        float x[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = live ? X[k * ntot + i] : 0.f;
+        float x[4];
+        load_features(X, ntot, i, live, x);
+        const float ti = live ? T[i] : 0.f;
+        const bf16x4 xb = xb_of(x);
         Fwd f;
-        mlp_fwd16(P, wbf, xb_of(x), f);
-        const float dy = live ? 2.f * (f.y - T[i]) * invB : 0.f;
-        if (l < 16 && live) err2 += (f.y - T[i]) * (f.y - T[i]);
-        if (l < 16) gb3 += dy;
-        // dZ2^T (D layout) and the per-hidden-unit sums
-        float dz2[4][4];
+        mlp_fwd16(net, xb, f);
+        const float err = live ? f.y - ti : 0.f, dy = 2.f * err * invB;
+        if (l < 16) {
+            err2 += err * err;
+            gb3 += dy;
+        }
+        // dZ2^T (D layout), the per-hidden-unit sums, and the LDS operands
         bf16x4 dz2b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int h = 16 * u + 4 * g + e;
                 const float h2 = f.h2[u][e];
                 gw3[u][e] += dy * h2;
-                const float d = P[MLP_OFF_W3 + h] * dy * (1.f - h2 * h2);
-                dz2[u][e] = d;
+                const float d = net.w3[u][e] * dy * (1.f - h2 * h2);
                 gb2[u][e] += d;
                 dz2b[u][e] = to_bf16(d);
             }
-        // transposes through LDS: sA[h][j] = dZ2^T, sB[h][j] = H1^T, sX[j][k] = X
-        __syncthreads();
+        __syncthreads();                           // the pass before has read its operands (and sWT is whole)
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int h = 16 * u + 4 * g + e;
-                sA[h * 16 + r] = dz2b[u][e];
-                sB[h * 16 + r] = to_bf16(f.h1[u][e]);
+                const int o = (16 * u + 4 * g + e) * GRAD_PITCH + 16 * w + r;
+                sA[o] = dz2b[u][e];
+                sB[o] = to_bf16(f.h1[u][e]);
             }
-        if (g < 4) {
+        if (g < 2) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sX[r * 16 + 4 * g + e] = (4 * g + e) < 8 ? to_bf16(x[4 * g + e]) : (short)0;
+            for (int e = 0; e < 4; ++e) sX[(4 * g + e) * GRAD_PITCH + 16 * w + r] = xb[e];
         }
-        __syncthreads();
-        // dW2[a][b] += sum_j dZ2^T[a][j] H1^T[b][j]: A[i][k=j] = sA[16u+i][j],
-        // B[k=j][n] = sB[16v+n][j]
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            bf16x4 a;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] = sA[(16 * u + r) * 16 + 4 * g + e];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                bf16x4 b;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) b[e] = sB[(16 * v + r) * 16 + 4 * g + e];
-                dW2[u][v] = mfma(a, b, dW2[u][v]);
-            }
-        }
-        // dH1^T = W2^T dZ2^T: A[i][k] = W2[16c+k][16v+i], B = dZ2^T tile c
+        // dH1^T = W2^T dZ2^T: A[i][k] = W2^T[16v+i][16c+k], B = dZ2^T tile c
         float dz1[4][4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                bf16x4 a;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) a[e] = (short)wbf[512 + (16 * c + 4 * g + e) * MLP_H + 16 * v + r];
-                z = mfma(a, dz2b[c], z);
-            }
+            for (int c = 0; c < 4; ++c)
+                z = mfma(*reinterpret_cast<const bf16x4*>(sWT + (16 * v + r) * GRAD_PITCH + 16 * c + 4 * g), dz2b[c], z);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float h1 = f.h1[v][e];
@@ -260,25 +257,29 @@ __global__ __launch_bounds__(64) void k_mlp_grad(long long i0, long long cnt, lo
             }
         }
         __syncthreads();
+        // dW2[a][b] += sum_j dZ2^T[a][j] H1^T[b][j], rows a of this wave:
+        // A[i][k=j] = sA[16w+i][j], B[k=j][n] = sB[16v+n][j]
+#pragma unroll
+        for (int q = 0; q < GRAD_SAMPLES / 16; ++q) {
+            const bf16x4 a = *reinterpret_cast<const bf16x4*>(row16 + 16 * q);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                dW2[v] = mfma(a, *reinterpret_cast<const bf16x4*>(sB + (16 * v + r) * GRAD_PITCH + 16 * q + 4 * g), dW2[v]);
+        }
+        __syncthreads();
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sA[(16 * v + 4 * g + e) * 16 + r] = to_bf16(dz1[v][e]);
+            for (int e = 0; e < 4; ++e) sA[(16 * v + 4 * g + e) * GRAD_PITCH + 16 * w + r] = to_bf16(dz1[v][e]);
         __syncthreads();
-        // dW1[a][k] += sum_j dZ1^T[a][j] X[j][k]: A[i][k=j] = sA[16u+i][j],
-        // B[k=j][n] = sX[j][n]
+        // dW1[a][k] += sum_j dZ1^T[a][j] X[j][k] (columns 8..15 of the tile unused)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            bf16x4 a, b;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = sA[(16 * u + r) * 16 + 4 * g + e];
-                b[e] = sX[(4 * g + e) * 16 + r];
-            }
-            dW1[u] = mfma(a, b, dW1[u]);
+        for (int q = 0; q < GRAD_SAMPLES / 16; ++q) {
+            const bf16x4 a = *reinterpret_cast<const bf16x4*>(row16 + 16 * q);
+            dW1 = mfma(a, *reinterpret_cast<const bf16x4*>(sX + (r & 7) * GRAD_PITCH + 16 * q + 4 * g), dW1);
         }
     }
-    // reduce and accumulate into the global gradient
+    // per-hidden-unit sums: over the 16 samples of the wave, then its waves
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -286,30 +287,51 @@ __global__ __launch_bounds__(64) void k_mlp_grad(long long i0, long long cnt, lo
             const int h = 16 * u + 4 * g + e;
             const float s3 = group16_sum(gw3[u][e]), s2 = group16_sum(gb2[u][e]), s1 = group16_sum(gb1[u][e]);
             if (r == 0) {
-                atomicAdd(&grad[MLP_OFF_W3 + h], s3);
-                atomicAdd(&grad[MLP_OFF_B2 + h], s2);
-                atomicAdd(&grad[MLP_OFF_B1 + h], s1);
+                sSum[w][h] = s3;
+                sSum[w][64 + h] = s2;
+                sSum[w][128 + h] = s1;
             }
         }
     gb3 = group16_sum(gb3);
     err2 = group16_sum(err2);
     if (l == 0) {
-        atomicAdd(&grad[MLP_OFF_B3], gb3);
-        atomicAdd(sse, err2);
+        sSum[w][192] = gb3;
+        sSum[w][193] = err2;
     }
-    // D layout: dW2 tile (u,v) element e of lane l = dW2[16u + 4g + e][16v + r]
+    // D layout: dW2 tile (w,v) element e of lane l = dW2[16w + 4g + e][16v + r]
+    float* const out = part + (long long)blockIdx.x * GRAD_STRIDE;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int e = 0; e < 4; ++e) out[MLP_OFF_W2 + (16 * w + 4 * g + e) * MLP_H + 16 * v + r] = dW2[v][e];
+    if (r < MLP_IN) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                atomicAdd(&grad[MLP_OFF_W2 + (16 * u + 4 * g + e) * MLP_H + 16 * v + r], dW2[u][v][e]);
-        if (r < MLP_IN) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) atomicAdd(&grad[MLP_OFF_W1 + (16 * u + 4 * g + e) * MLP_IN + r], dW1[u][e]);
-        }
+        for (int e = 0; e < 4; ++e) out[MLP_OFF_W1 + (16 * w + 4 * g + e) * MLP_IN + r] = dW1[e];
     }
+    __syncthreads();
+    if (threadIdx.x < 194) {
+        const int q = threadIdx.x;
+        const float s = (sSum[0][q] + sSum[1][q]) + (sSum[2][q] + sSum[3][q]);
+        const int o = q < 64 ? MLP_OFF_W3 + q : (q < 128 ? MLP_OFF_B2 + q - 64 : (q < 192 ? MLP_OFF_B1 + q - 128
+                                                                                 : (q == 192 ? MLP_OFF_B3 : GRAD_SSE)));
+        out[o] = s;
+    }
+}
+
+// Sum over the blocks' partial gradients of the parameter this thread's lane
+// owns (64 parameters per block; the four waves share the partials), valid
+// in wave 0.
+__device__ __forceinline__ float grad_total(const float* __restrict__ part, int nblk, int p, float (*sPart)[64])
+{
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    float s = 0.f;
+    if (p <= GRAD_SSE) {
+#pragma unroll 8
+        for (int b = w; b < nblk; b += 4) s += part[(long long)b * GRAD_STRIDE + p];
+    }
+    sPart[w][l] = s;
+    __syncthreads();
+    return (sPart[0][l] + sPart[1][l]) + (sPart[2][l] + sPart[3][l]);
 }
 
 __global__ void k_fill_f32(float* p, long long n, float v)
@@ -319,14 +341,35 @@ __global__ void k_fill_f32(float* p, long long n, float v)
         p[i] = v;
 }
 
-hipError_t launch_mlp_grad(long long i0, long long cnt, long long ntot, float invB, const float* X, const float* T,
-                           const MlpDev& m, float* grad, float* sse, hipStream_t s)
+// At most GRAD_MAX_BLOCKS blocks (one per CU; the partials are read back by
+// the sum).
+int mlp_grad_blocks(long long cnt)
 {
-    const long long per = GRAD_CHUNKS * 16;
-    const long long nb = (cnt + per - 1) / per;
+    const long long nb = (cnt + GRAD_SAMPLES - 1) / GRAD_SAMPLES;
+    return (int)(nb < GRAD_MAX_BLOCKS ? nb : GRAD_MAX_BLOCKS);
+}
+
+hipError_t launch_mlp_grad(long long i0, long long cnt, long long ntot, float invB, const float* X, const float* T,
+                           const MlpDev& m, float* part, hipStream_t s)
+{
+    const int nb = mlp_grad_blocks(cnt);
     if (nb < 1) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nb), dim3(64), 0, s, i0, cnt, ntot, invB, X, T, m.master, m.wbf,
-                       grad, sse);
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(256), 0, s, i0, cnt, ntot, invB, X, T, m.master, m.wbf, part);
+    return hipGetLastError();
+}
+
+// grad[0 .. MLP_NPARAM] = the summed gradient, then the sum of squared errors.
+__global__ __launch_bounds__(256) void k_grad_sum(const float* __restrict__ part, int nblk, float* __restrict__ grad)
+{
+    __shared__ float sPart[4][64];
+    const int p = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float g = grad_total(part, nblk, p, sPart);
+    if (threadIdx.x < 64 && p <= GRAD_SSE) grad[p] = g;
+}
+
+hipError_t launch_grad_sum(const float* part, int nblk, float* grad, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_grad_sum, dim3((GRAD_SSE + 64) / 64), dim3(256), 0, s, part, nblk, grad);
     return hipGetLastError();
 }
 
@@ -339,31 +382,38 @@ hipError_t launch_fill_f32(float* p, long long n, float v, hipStream_t s)
     return hipGetLastError();
 }
 
-// Adam (Kingma and Ba) on the FP32 master parameters, then refresh the BF16
-// copies and clear the gradient for the next minibatch.
+// Adam (Kingma and Ba) on the FP32 master parameters from the blocks' partial
+// gradients, then refresh the BF16 copies; the sum of squared errors is added
+// to *sse.
 __global__ __launch_bounds__(256) void k_adam(float* __restrict__ P, uint16_t* __restrict__ wbf,
-                                              float* __restrict__ m, float* __restrict__ v, float* __restrict__ grad,
+                                              float* __restrict__ m, float* __restrict__ v,
+                                              const float* __restrict__ part, int nblk, float* __restrict__ sse,
                                               float lr, float b1, float b2, float eps, float c1, float c2)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < MLP_NPARAM; i += gridDim.x * blockDim.x) {
-        const float gi = grad[i];
-        const float mi = b1 * m[i] + (1.f - b1) * gi;
-        const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float p = P[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        P[i] = p;
-        grad[i] = 0.f;
-        if (i < MLP_OFF_B1) wbf[i] = (uint16_t)to_bf16(p);
-        else if (i >= MLP_OFF_W2 && i < MLP_OFF_B2) wbf[512 + (i - MLP_OFF_W2)] = (uint16_t)to_bf16(p);
+    __shared__ float sPart[4][64];
+    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
+    const float gi = grad_total(part, nblk, i, sPart);
+    if (threadIdx.x >= 64 || i > GRAD_SSE) return;
+    if (i == GRAD_SSE) {
+        *sse += gi;
+        return;
     }
+    const float mi = b1 * m[i] + (1.f - b1) * gi;
+    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+    m[i] = mi;
+    v[i] = vi;
+    const float p = P[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    P[i] = p;
+    if (i < MLP_OFF_B1) wbf[i] = (uint16_t)to_bf16(p);
+    else if (i >= MLP_OFF_W2 && i < MLP_OFF_B2) wbf[512 + (i - MLP_OFF_W2)] = (uint16_t)to_bf16(p);
 }
 
-hipError_t launch_adam(const MlpDev& md, float* m, float* v, float* grad, float lr, float b1, float b2, float eps,
-                       int step, hipStream_t s)
+hipError_t launch_adam(const MlpDev& md, float* m, float* v, const float* part, int nblk, float* sse, float lr,
+                       float b1, float b2, float eps, int step, hipStream_t s)
 {
     const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3(19), dim3(256), 0, s, md.master, md.wbf, m, v, grad, lr, b1, b2, eps, c1, c2);
+    hipLaunchKernelGGL(k_adam, dim3((GRAD_SSE + 64) / 64), dim3(256), 0, s, md.master, md.wbf, m, v, part, nblk, sse,
+                       lr, b1, b2, eps, c1, c2);
     return hipGetLastError();
 }
 

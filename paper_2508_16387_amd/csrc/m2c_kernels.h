@@ -137,11 +137,15 @@ struct MlpDev;
 hipError_t launch_mlp_features(long long n, const double* in, const double* eos, const double* ps, float* X,
                                float* tg, hipStream_t s);
 hipError_t launch_mlp_forward(long long n, const float* X, const MlpDev& m, float* y, hipStream_t s);
+// gradient of samples [i0, i0 + cnt) as partial sums, one per block of
+// mlp_grad_blocks(cnt), at part[block][GRAD_STRIDE]
+int mlp_grad_blocks(long long cnt);
 hipError_t launch_mlp_grad(long long i0, long long cnt, long long ntot, float invB, const float* X, const float* T,
-                           const MlpDev& m, float* grad, float* sse, hipStream_t s);
+                           const MlpDev& m, float* part, hipStream_t s);
+hipError_t launch_grad_sum(const float* part, int nblk, float* grad, hipStream_t s);
 hipError_t launch_fill_f32(float* p, long long n, float v, hipStream_t s);
-hipError_t launch_adam(const MlpDev& md, float* m, float* v, float* grad, float lr, float b1, float b2, float eps,
-                       int step, hipStream_t s);
+hipError_t launch_adam(const MlpDev& md, float* m, float* v, const float* part, int nblk, float* sse, float lr,
+                       float b1, float b2, float eps, int step, hipStream_t s);
 hipError_t launch_mlp_sync(const MlpDev& m, hipStream_t s);
 hipError_t launch_points_guess(long long n, const double* in, const double* eos, const MlpDev& m, double* guess,
                                hipStream_t s);

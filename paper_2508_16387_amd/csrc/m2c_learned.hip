@@ -166,14 +166,15 @@ int m2c_mlp_grad(const m2c_mlp* m, int64_t n, const float* X8, const float* t, f
 {
     if (!m || n < 1 || !X8 || !t || !grad) return M2C_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    float* dg = nullptr;
-    if (hipMalloc((void**)&dg, (MLP_NPARAM + 1) * sizeof(float)) != hipSuccess) return M2C_ERR_NOMEM;
+    float* dg = nullptr;                        // gradient and squared error | partial gradients
+    const int nb = mlp_grad_blocks(n);
+    if (hipMalloc((void**)&dg, (size_t)GRAD_STRIDE * (nb + 1) * sizeof(float)) != hipSuccess) return M2C_ERR_NOMEM;
     int rc = M2C_OK;
     float sse = 0.0f;
-    if (launch_fill_f32(dg, MLP_NPARAM + 1, 0.0f, s) != hipSuccess ||
-        launch_mlp_grad(0, n, n, 1.0f / (float)n, X8, t, m->d, dg, dg + MLP_NPARAM, s) != hipSuccess ||
+    if (launch_mlp_grad(0, n, n, 1.0f / (float)n, X8, t, m->d, dg + GRAD_STRIDE, s) != hipSuccess ||
+        launch_grad_sum(dg + GRAD_STRIDE, nb, dg, s) != hipSuccess ||
         hipMemcpyAsync(grad, dg, MLP_NPARAM * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&sse, dg + MLP_NPARAM, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipMemcpyAsync(&sse, dg + GRAD_SSE, sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         rc = M2C_ERR_DEVICE;
     (void)hipFree(dg);
@@ -187,16 +188,17 @@ int m2c_mlp_train(m2c_mlp* m, int64_t n, const float* X8, const float* t, const 
     if (!m || n < 1 || !X8 || !t || !o || o->struct_size != sizeof(m2c_train_opts)) return M2C_ERR_ARG;
     if (o->epochs < 1 || o->batch < 16 || !(o->lr > 0.0f) || !(o->lr_final > 0.0f)) return M2C_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    float* buf = nullptr;                       // grad | m | v | sse
-    const size_t nb = 3 * (size_t)MLP_NPARAM + 1;
-    if (hipSetDevice(m->device) != hipSuccess) return M2C_ERR_DEVICE;
-    if (hipMalloc((void**)&buf, nb * sizeof(float)) != hipSuccess) return M2C_ERR_NOMEM;
-    float* grad = buf;
-    float* mo = buf + MLP_NPARAM;
-    float* ve = buf + 2 * MLP_NPARAM;
-    float* sse = buf + 3 * MLP_NPARAM;
-    int rc = launch_fill_f32(buf, (long long)nb, 0.0f, s) == hipSuccess ? M2C_OK : M2C_ERR_DEVICE;
+    float* buf = nullptr;                       // m | v | sse | partial gradients
     const long long B = o->batch;
+    const size_t state = 2 * (size_t)MLP_NPARAM + 1;
+    const size_t parts = (size_t)GRAD_STRIDE * mlp_grad_blocks(n < B ? n : B);
+    if (hipSetDevice(m->device) != hipSuccess) return M2C_ERR_DEVICE;
+    if (hipMalloc((void**)&buf, (state + parts) * sizeof(float)) != hipSuccess) return M2C_ERR_NOMEM;
+    float* mo = buf;
+    float* ve = buf + MLP_NPARAM;
+    float* sse = buf + 2 * MLP_NPARAM;
+    float* part = buf + state;
+    int rc = launch_fill_f32(buf, (long long)state, 0.0f, s) == hipSuccess ? M2C_OK : M2C_ERR_DEVICE;
     const long long nbatch = (n + B - 1) / B;
     const long long total = nbatch * o->epochs;
     long long step = 0;
@@ -205,8 +207,8 @@ int m2c_mlp_train(m2c_mlp* m, int64_t n, const float* X8, const float* t, const 
             const long long i0 = bi * B, cnt = (i0 + B <= n) ? B : n - i0;
             ++step;
             const float lr = o->lr * std::pow(o->lr_final / o->lr, (float)(step - 1) / (float)(total > 1 ? total - 1 : 1));
-            if (launch_mlp_grad(i0, cnt, n, 1.0f / (float)cnt, X8, t, m->d, grad, sse, s) != hipSuccess ||
-                launch_adam(m->d, mo, ve, grad, lr, o->beta1, o->beta2, o->eps, (int)step, s) != hipSuccess)
+            if (launch_mlp_grad(i0, cnt, n, 1.0f / (float)cnt, X8, t, m->d, part, s) != hipSuccess ||
+                launch_adam(m->d, mo, ve, part, mlp_grad_blocks(cnt), sse, lr, o->beta1, o->beta2, o->eps, (int)step, s) != hipSuccess)
                 rc = M2C_ERR_DEVICE;
         }
         if (rc == M2C_OK && loss_per_epoch) {

@@ -16,6 +16,9 @@ constexpr int MLP_IN = 8, MLP_H = 64;
 constexpr int MLP_OFF_W1 = 0, MLP_OFF_B1 = 512, MLP_OFF_W2 = 576, MLP_OFF_B2 = 4672, MLP_OFF_W3 = 4736,
               MLP_OFF_B3 = 4800, MLP_NPARAM = 4801;
 constexpr int MLP_NBF = 512 + 4096;            // BF16 copies: W1 then W2
+// Partial gradients of the training kernel: per block the parameters'
+// gradient, the sum of squared errors, padding.
+constexpr int GRAD_SSE = MLP_NPARAM, GRAD_STRIDE = 4864, GRAD_MAX_BLOCKS = 256;
 
 struct MlpDev {
     float* master;                             // [MLP_NPARAM]

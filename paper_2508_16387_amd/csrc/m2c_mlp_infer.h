@@ -27,6 +27,12 @@ __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
+// Four consecutive weights, biases or samples in one load.  The network's
+// arrays are allocations of their own and every offset taken here is a
+// multiple of four elements, so the loads are aligned.
+__device__ __forceinline__ bf16x4 ld_bf16x4(const uint16_t* p) { return *reinterpret_cast<const bf16x4*>(p); }
+__device__ __forceinline__ f32x4 ld_f32x4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+
 // ---------------------------------------------------------------------------
 // Inference for the guess kernels.  A wave keeps the weights in registers
 // (the A operands of layers 1 and 2, and its lanes' biases and output
@@ -42,20 +48,20 @@ __device__ __forceinline__ void mlp_load_regs(const float* __restrict__ P, const
                                               MlpRegs& w)
 {
     const int l = threadIdx.x & 63, g = l >> 4, r = l & 15;
+    const bf16x4 zero = {0, 0, 0, 0};
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
+        w.a1[t] = g < 2 ? ld_bf16x4(wbf + MLP_OFF_W1 + (16 * t + r) * MLP_IN + 4 * g) : zero;
+        const f32x4 b1 = ld_f32x4(P + MLP_OFF_B1 + 16 * t + 4 * g), b2 = ld_f32x4(P + MLP_OFF_B2 + 16 * t + 4 * g),
+                    w3 = ld_f32x4(P + MLP_OFF_W3 + 16 * t + 4 * g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int k = 4 * g + e, h = 16 * t + 4 * g + e;
-            w.a1[t][e] = k < MLP_IN ? (short)wbf[MLP_OFF_W1 + (16 * t + r) * MLP_IN + k] : (short)0;
-            w.b1[t][e] = P[MLP_OFF_B1 + h];
-            w.b2[t][e] = P[MLP_OFF_B2 + h];
-            w.w3[t][e] = P[MLP_OFF_W3 + h];
+            w.b1[t][e] = b1[e];
+            w.b2[t][e] = b2[e];
+            w.w3[t][e] = w3[e];
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w.a2[t][c][e] = (short)wbf[512 + (16 * t + r) * MLP_H + 16 * c + 4 * g + e];
+        for (int c = 0; c < 4; ++c) w.a2[t][c] = ld_bf16x4(wbf + 512 + (16 * t + r) * MLP_H + 16 * c + 4 * g);
     }
     w.b3 = P[MLP_OFF_B3];
 }
@@ -142,15 +148,12 @@ __device__ __forceinline__ float mlp_infer16_mem(const float* __restrict__ P, co
     bf16x4 hb[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        bf16x4 a1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int k = 4 * g + e;
-            a1[e] = k < MLP_IN ? (short)wbf[MLP_OFF_W1 + (16 * t + r) * MLP_IN + k] : (short)0;
-        }
+        bf16x4 a1 = {0, 0, 0, 0};
+        if (g < 2) a1 = ld_bf16x4(wbf + MLP_OFF_W1 + (16 * t + r) * MLP_IN + 4 * g);
         const f32x4 z = mfma(a1, xb, f32x4{0.f, 0.f, 0.f, 0.f});
+        const f32x4 b1 = ld_f32x4(P + MLP_OFF_B1 + 16 * t + 4 * g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) hb[t][e] = to_bf16(tanh_fast(z[e] + P[MLP_OFF_B1 + 16 * t + 4 * g + e]));
+        for (int e = 0; e < 4; ++e) hb[t][e] = to_bf16(tanh_fast(z[e] + b1[e]));
     }
     float part = 0.f;
 #pragma unroll 1
@@ -158,16 +161,11 @@ __device__ __forceinline__ float mlp_infer16_mem(const float* __restrict__ P, co
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            bf16x4 a2;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) a2[e] = (short)wbf[512 + (16 * u + r) * MLP_H + 16 * c + 4 * g + e];
-            z = mfma(a2, hb[c], z);
+            z = mfma(ld_bf16x4(wbf + 512 + (16 * u + r) * MLP_H + 16 * c + 4 * g), hb[c], z);
         }
+        const f32x4 b2 = ld_f32x4(P + MLP_OFF_B2 + 16 * u + 4 * g), w3 = ld_f32x4(P + MLP_OFF_W3 + 16 * u + 4 * g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int h = 16 * u + 4 * g + e;
-            part += P[MLP_OFF_W3 + h] * tanh_fast(z[e] + P[MLP_OFF_B2 + h]);
-        }
+        for (int e = 0; e < 4; ++e) part += w3[e] * tanh_fast(z[e] + b2[e]);
     }
     part += __shfl_xor(part, 16);
     part += __shfl_xor(part, 32);

@@ -11,9 +11,18 @@
 // wavefronts would otherwise diverge on the Newton iteration.
 //
 // Queue order is ascending face id f = 3c + d (face between cell c and its
-// +d neighbour); the compaction is a deterministic three-pass scan
-// (per-block count, one-block exclusive scan, scatter with wavefront prefix
-// sums), so the queue is bit-identical from run to run.  The face -> slot
+// +d neighbour); the compaction is deterministic (counts per block, then
+// each block adds up the counts before its own and writes its faces with
+// wavefront prefix sums), so the queue is bit-identical from run to run.
+//
+// Launches of a single-grid step besides its bulk stages: k_step_begin (the
+// phase update of the step before, the counts), then per Runge-Kutta stage
+// one FIVER launch, the first of which also writes a rebuilt queue and opens
+// the step.  Each is a chain of a few dependent memory accesses whatever its
+// size, so a launch saved is its whole time saved: count, scan and scatter
+// as launches of their own took 4.5 + 4.6 + 4.8 us of a 128^3 step; now 5.0
+// and 0.5 more for the first FIVER launch.  General EOS, 128^3 charge, whose
+// queue is rebuilt in every step: 40 -> 24 us.  The face -> slot
 // map is written only at the faces of the new queue and read only at faces
 // whose cells differ in material under the same frozen ids, so entries left
 // from earlier queues are never read and need no clearing.
@@ -186,16 +195,10 @@ __device__ __forceinline__ void count_body(const IfaceArgs& a, int blk)
 
 // A step whose predecessor flipped no cell has the material ids the queue
 // was built from (the last stage writes every id, and a flip is exactly a
-// changed id), so the single-grid compaction keeps the queue and the face
-// slots.  The decision is read here before the scan kernel clears the flip
-// count, and the scan records it for the scatter.
+// changed id), so the compaction keeps the queue and the face slots.  The
+// decision is taken before the flip count is cleared, and recorded for the
+// scatter.
 __device__ __forceinline__ bool queue_kept(const DevScalars* sc) { return sc->qvalid && sc->nflip == 0; }
-
-__global__ __launch_bounds__(COMPACT_THREADS) void k_count(const IfaceArgs a)
-{
-    if (queue_kept(a.sc)) return;
-    count_body(a, blockIdx.x);
-}
 
 // One block: exclusive scan of the block counts (in place), total -> qlen.
 // Each thread sums a contiguous segment of the counts, the block scans the
@@ -236,6 +239,16 @@ __device__ __forceinline__ void scan_body(const IfaceArgs& a)
     }
 }
 
+// Sum of the counts of blocks [0, nb), for every thread of the block.
+__device__ __forceinline__ int count_prefix(const IfaceArgs& a, int nb)
+{
+    __shared__ int sRed[COMPACT_THREADS / 64];
+    int v = 0;
+    for (int b = threadIdx.x; b < nb; b += COMPACT_THREADS) v += a.blockcnt[b];
+    __syncthreads();                              // sRed of an earlier call
+    return block_sum(v, sRed);
+}
+
 // End of a step (single grid): counters and simulated time, only when no
 // kernel of the step reported an error.
 __device__ __forceinline__ void end_step_body(DevScalars* sc, int stages)
@@ -264,26 +277,23 @@ __device__ __forceinline__ void begin_step_body(DevScalars* sc, double cfl, doub
     sc->nflip = 0;
 }
 
-// The scan kernel of a step also closes the previous step of the same
-// m2c_step call (end_prev) and opens this one (begin): both must precede
-// every kernel that reads dt, and follow the phase update of the previous
-// step, which is where the single-block scan sits in the stream.
-__global__ __launch_bounds__(1024) void k_scan(const IfaceArgs a, int end_prev, int begin, double cfl,
-                                               double dt_fixed, double dt_imposed)
+// Opens a step in one block of the launch that follows k_step_begin: ends
+// the previous step of the same m2c_step call (end_prev), forms dt (begin)
+// and, when the queue was rebuilt, records its length.  The other blocks of
+// the launch read none of what it writes.
+__device__ __forceinline__ void open_step(const IfaceArgs& a, const StepOpen& o)
 {
-    __shared__ int sKeep;
-    if (threadIdx.x == 0) {
-        const int keep = queue_kept(a.sc) ? 1 : 0;
-        sKeep = keep;
-        a.sc->qreuse = keep;
-        if (end_prev) end_step_body(a.sc, a.g.rk_stages);
-        if (begin) begin_step_body(a.sc, cfl, dt_fixed, dt_imposed);
-    }
-    __syncthreads();
-    if (sKeep) return;
-    scan_body(a);
-    // the scatter that follows completes the queue unless a kernel failed
-    if (threadIdx.x == 0) a.sc->qvalid = a.sc->err == 0 ? 1 : 0;
+    DevScalars* sc = a.sc;
+    const bool rebuilt = !sc->qreuse;
+    const int total = rebuilt ? count_prefix(a, a.nblk) : 0;
+    if (threadIdx.x != 0) return;
+    if (o.end_prev) end_step_body(sc, a.g.rk_stages);
+    if (o.begin) begin_step_body(sc, a.g.cfl, a.g.dt_fixed, o.dt_imposed);
+    if (!rebuilt) return;
+    // (a queue past its capacity is not written, see scatter_body)
+    if (total > a.qcap) atomicCAS(&sc->err, 0, ST_OVERFLOW);
+    sc->qlen = total > a.qcap ? 0 : total;
+    sc->qvalid = sc->err == 0 ? 1 : 0;
 }
 
 __global__ void k_end_step(DevScalars* sc, int stages) { end_step_body(sc, stages); }
@@ -294,10 +304,12 @@ hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s)
     return hipGetLastError();
 }
 
-__device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk)
+// Writes the queue entries and face slots of compaction block blk, from
+// queue position base; returns their number (0, with nothing written, where
+// they would pass the queue's capacity).
+__device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int base)
 {
     __shared__ int sW[COMPACT_THREADS / 64];
-    if (a.sc->err != 0) return;
     const uint32_t wbase = compact_wave_base(blk);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const bool words = compact_words(a.g, a.chi);
@@ -306,8 +318,11 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk)
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o);
     if (lane == 0) sW[w] = cnt;
     __syncthreads();
-    if (cnt == 0) return;                     // wave-uniform
-    int off = a.blockcnt[blk];
+    int total = 0;
+    for (int k = 0; k < COMPACT_THREADS / 64; ++k) total += sW[k];
+    if ((long long)base + total > a.qcap) return 0;
+    if (cnt == 0) return total;               // wave-uniform
+    int off = base;
     for (int k = 0; k < w; ++k) off += sW[k];
     if (words) {
         // the lane's 16 cells are 4 runs of 4 consecutive cells; faces in
@@ -332,7 +347,7 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk)
                 }
             off += tot;
         }
-        return;
+        return total;
     }
     // byte path: faces in ascending id order: by cell, then by axis
     const uint64_t below = (1ull << lane) - 1ull;
@@ -351,14 +366,28 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk)
             }
         off += __popcll(b0) + __popcll(b1) + __popcll(b2);
     }
+    return total;
 }
 
-__global__ __launch_bounds__(COMPACT_THREADS) void k_scatter(const IfaceArgs a)
+// The queue alone: the step with a general EOS, and listing the interface
+// faces between steps.
+__global__ __launch_bounds__(COMPACT_THREADS) void k_scatter(const IfaceArgs a, const StepOpen o)
 {
+    if (blockIdx.x == 0) open_step(a, o);
     if (a.sc->qreuse) return;
-    scatter_body(a, blockIdx.x);
+    for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) scatter_body(a, cb, count_prefix(a, cb));
 }
 
+// Blocks of the compaction launches: at most four per CU, since the launch
+// also runs, to no purpose but its time, when the queue is kept (384^3: 13824
+// blocks that return at once took 5 us).
+unsigned compact_grid(int nblk) { return (unsigned)(nblk < 1024 ? nblk : 1024); }
+
+hipError_t launch_scatter(const IfaceArgs& a, const StepOpen& o, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_scatter, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, o);
+    return hipGetLastError();
+}
 
 // ---------------------------------------------------------------------------
 // FIVER: one thread per queued face.  The Riemann data are the two cells'
@@ -398,38 +427,61 @@ __device__ __forceinline__ void cell_prim(const Grid& G, const eos::EosK* sEos, 
 // F0, F1 (EG): families of materials 0 and 1 fixed at compile time, so that
 // a kernel carries the wave curves and EOS forms of those two families only
 // (-1: dispatched at run time).
+// open (nullable): the first launch of a step, which opens it and writes a
+// rebuilt queue: compaction block blk writes its part and then solves just
+// that part (its faces are then spread over the blocks as the interface lies
+// in the grid, which costs little for stiffened gases, and saves a launch).
 template <bool EG, bool LG = false, int F0 = -1, int F1 = -1>
-__device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int blk, int nblk,
+__device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int blk, int nblk, const StepOpen* open,
                                            const MlpDev* m = nullptr)
 {
     static_assert(!(EG && LG) || (F0 >= 0 && F1 >= 0), "the general-EOS learned start needs the families");
     __shared__ unsigned long long sCnt[3][4];
-    __shared__ int sErr;
+    __shared__ int sHead[2];
     __shared__ eos::EosK sEos[EG ? 2 : 1];
     DevScalars* sc = a.sc;
-    // skip when an earlier kernel failed; read once so that the whole block
-    // takes the same branch (this kernel's own reports may raise the flag)
-    if (threadIdx.x == 0) sErr = sc->err;
-    if (EG && threadIdx.x == 0) {
-        const double* src = reinterpret_cast<const double*>(a.g.ek);
-        double* dst = reinterpret_cast<double*>(sEos);
-#pragma unroll
-        for (int t = 0; t < (int)(2 * sizeof(eos::EosK) / sizeof(double)); ++t) dst[t] = src[t];
-    }
-    __syncthreads();
-    if (sErr != 0) return;
     const Grid& G = a.g;
     constexpr int FS = eos::fam_set(F0) | eos::fam_set(F1);
-    const int n = sc->qlen;
+    // nothing to do when an earlier kernel failed; read once per block so that
+    // the whole block takes the same branch (this kernel's own reports may
+    // raise the flag meanwhile)
+    const int q0 = blk * (int)blockDim.x + (int)threadIdx.x;
+    // the thread's first entry of a kept queue, read beside the scalars that
+    // say whether it counts (each dependent read is about 0.7 us of a launch
+    // that takes 8 for a single face)
+    const int32_t ahead = q0 < a.qcap ? a.queue[q0] : 0;
+    if (threadIdx.x == 0) {
+        const int err = sc->err, qlen = sc->qlen, reuse = sc->qreuse;
+        sHead[0] = err != 0 ? 0 : (open && !reuse ? 1 : qlen);
+        sHead[1] = open && !reuse;
+    }
+    if (EG) geos_stage(G, sEos);
+    else __syncthreads();
+    const bool rebuilt = open && sHead[1];
+    int lo = 0, n = sHead[0];
+    if (open && blk == 0) open_step(a, *open);
     long long iters = 0, fallbacks = 0, mlp_fb = 0;
-    const int stride = nblk * blockDim.x;
+    // A kept queue in one sweep of the launch, a rebuilt one compaction block
+    // by compaction block.  (Whole wavefronts of 64 faces and whole blocks
+    // first: a short queue spread over more wavefronts at 8 faces each took
+    // longer: 128^3 charge 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
+    const int stride = (rebuilt ? 1 : nblk) * (int)blockDim.x, known = rebuilt ? -1 : q0;
+    int first = q0;
+    if (rebuilt && (n == 0 || blk >= a.nblk)) {
+        n = 0;
+    } else if (rebuilt) {                                            // block-uniform
+        lo = count_prefix(a, blk);
+        n = lo + scatter_body(a, blk, lo);
+        first = lo + (int)threadIdx.x;
+        __syncthreads();                                             // the block reads its own entries
+    }
     // LG: wave-uniform trip count (q may pass n in the last pass)
     const int qend = LG ? (n + 63) / 64 * 64 : n;
-    for (int q = blk * blockDim.x + threadIdx.x; q < qend; q += stride) {
+    for (int q = first; q < qend; q += stride) {
         const bool live = !LG || q < n;
         uint32_t c = 0, cn = 0;
         int d = 0;
-        if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)a.queue[q], c, cn, d);
+        if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)(q == known ? ahead : a.queue[q]), c, cn, d);
         const int xa = live ? a.chi[c] : 0, xb = live ? a.chi[cn] : 0;
         double qa[5], qb[5];
         cell_prim<EG, FS>(G, sEos, a.Win, c, xa, qa);
@@ -562,22 +614,29 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     }
 }
 
+static_assert(COMPACT_THREADS == 256, "the FIVER kernels run compaction blocks");
+
 __global__ __launch_bounds__(256) void k_fiver(const IfaceArgs a, int record)
 {
-    fiver_body<false>(a, record, blockIdx.x, gridDim.x);
+    fiver_body<false>(a, record, blockIdx.x, gridDim.x, nullptr);
+}
+
+__global__ __launch_bounds__(256) void k_fiver_open(const IfaceArgs a, int record, const StepOpen o)
+{
+    fiver_body<false>(a, record, blockIdx.x, gridDim.x, &o);
 }
 
 template <int F0, int F1>
 __global__ __launch_bounds__(256) void k_fiver_eos(const IfaceArgs a, int record)
 {
-    fiver_body<true, false, F0, F1>(a, record, blockIdx.x, gridDim.x);
+    fiver_body<true, false, F0, F1>(a, record, blockIdx.x, gridDim.x, nullptr);
 }
 
 // with the learned start, for the family pairs that take it (learned_pair)
 template <int F0, int F1>
 __global__ __launch_bounds__(256) void k_fiver_eos_learned(const IfaceArgs a, int record, const MlpDev m)
 {
-    fiver_body<true, true, F0, F1>(a, record, blockIdx.x, gridDim.x, &m);
+    fiver_body<true, true, F0, F1>(a, record, blockIdx.x, gridDim.x, nullptr, &m);
 }
 
 template <int F0, int F1>
@@ -600,22 +659,40 @@ static_assert(M2C_EOS_NASG == 0 && M2C_EOS_MG == 1 && M2C_EOS_JWL == 2, "family-
 
 __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int record, const MlpDev m)
 {
-    fiver_body<false, true>(a, record, blockIdx.x, gridDim.x, &m);
+    fiver_body<false, true>(a, record, blockIdx.x, gridDim.x, nullptr, &m);
 }
 
-hipError_t launch_fiver(const IfaceArgs& a, bool record, const MlpDev* mlp, hipStream_t s)
+hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s)
 {
     long long nb = (a.qcap + 255) / 256;
     if (nb > 1024) nb = 1024;
     if (nb < 1) nb = 1;
+    const int rec = record ? 1 : 0;
+    // with a general EOS the queue is a launch of its own: a face takes so
+    // long there that spreading the faces as the interface lies in the grid
+    // costs more than the launch (128^3 charge: FIVER 80 -> 131 us); with the
+    // learned guess too, whose network takes whole wavefronts of faces; and
+    // on grids of more compaction blocks than this kernel's registers let
+    // run at once, where the scan for them is work, not latency (384^3: 64
+    // against 30 us, of a 5 ms step)
+    if (open && (a.g.eosg || mlp || a.nblk > 512)) {
+        const hipError_t e = launch_scatter(a, *open, s);
+        if (e != hipSuccess) return e;
+        open = nullptr;
+    }
     if (a.g.eosg) {
         const int f0 = a.g.ek[0].fam, f1 = a.g.ek[1].fam;
         if (f0 < 0 || f0 > 2 || f1 < 0 || f1 > 2) return hipErrorInvalidValue;
-        kFiverEos[3 * f0 + f1](a, (unsigned)nb, record ? 1 : 0, mlp, s);
-    } else if (mlp)
-        hipLaunchKernelGGL(k_fiver_learned, dim3((unsigned)nb), dim3(256), 0, s, a, record ? 1 : 0, *mlp);
-    else
-        hipLaunchKernelGGL(k_fiver, dim3((unsigned)nb), dim3(256), 0, s, a, record ? 1 : 0);
+        kFiverEos[3 * f0 + f1](a, (unsigned)nb, rec, mlp, s);
+    } else if (mlp) {
+        hipLaunchKernelGGL(k_fiver_learned, dim3((unsigned)nb), dim3(256), 0, s, a, rec, *mlp);
+    } else if (open) {
+        // a rebuilt queue takes a block per compaction block
+        if (nb < a.nblk) nb = a.nblk;
+        hipLaunchKernelGGL(k_fiver_open, dim3((unsigned)nb), dim3(256), 0, s, a, rec, *open);
+    } else {
+        hipLaunchKernelGGL(k_fiver, dim3((unsigned)nb), dim3(256), 0, s, a, rec);
+    }
     return hipGetLastError();
 }
 
@@ -639,42 +716,62 @@ __device__ __forceinline__ void phase_body(const PhaseArgs& a, int blk, int nblk
     if (sc->err != 0) return;
     const int n = sc->nflip;
     const long long N = G.N, sxy = (long long)G.nx * G.ny, Q = a.qcap;
-    const long long cstr[3] = {1, G.nx, sxy};
-    const int nd[3] = {G.nx, G.ny, G.nz};
     double lam = 0.0;
     long long orphans = 0;
     for (int e = blk * blockDim.x + threadIdx.x; e < n; e += nblk * blockDim.x) {
         const long long c = a.flips[e];
         const int A = a.chi_old[c], B = a.chi_new[c];
-        const int k = (int)(c / sxy);
-        const long long r = c - (long long)k * sxy;
-        const int j = (int)(r / G.nx);
-        const int i = (int)(r - (long long)j * G.nx);
-        const int ijk[3] = {i, j, k};
+        // (32-bit: grids hold at most 2^29 cells)
+        const uint32_t c32 = (uint32_t)c, pl = (uint32_t)sxy;
+        const int k = (int)(c32 / pl);
+        const uint32_t r = c32 - (uint32_t)k * pl;
+        const int j = (int)(r / (uint32_t)G.nx);
+        const int i = (int)(r - (uint32_t)j * (uint32_t)G.nx);
+        // the six faces side by side: neighbours' ids, then the queue slots
+        // of the faces whose neighbour held B, then their star states (three
+        // memory latencies instead of three per face); summed in the order
+        // of the faces
+        long long lower[6];
+        bool held[6];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const int d = f / 2, side = f % 2;
+            const int nd = d == 0 ? G.nx : (d == 1 ? G.ny : G.nz), at = d == 0 ? i : (d == 1 ? j : k);
+            const long long str = d == 0 ? 1 : (d == 1 ? (long long)G.nx : sxy);
+            int nb = at + (side ? 1 : -1);
+            const bool out = nb < 0 || nb >= nd;
+            if (out) nb = side ? 0 : nd - 1;
+            const bool face = G.act[d] && (!out || G.bc[f] == BC_PERIODIC);
+            const long long ck = face ? c + (long long)(nb - at) * str : c;
+            lower[f] = side ? c : ck;
+            held[f] = face && a.chi_old[ck] == B;
+        }
+        int sl[6];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) sl[f] = held[f] ? a.fslot[3 * lower[f] + f / 2] : -1;
+        double st[6][5];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            const int side = f % 2;
+            if (sl[f] >= 0) {
+                st[f][0] = a.star[(side ? 3 : 2) * Q + sl[f]];
+                st[f][1] = a.star[1 * Q + sl[f]];
+                st[f][2] = a.star[(side ? 6 : 4) * Q + sl[f]];
+                st[f][3] = a.star[(side ? 7 : 5) * Q + sl[f]];
+                st[f][4] = a.star[0 * Q + sl[f]];
+            }
+        }
         double sum[5] = {0, 0, 0, 0, 0};
         int cnt = 0;
-        for (int d = 0; d < 3; ++d) {
-            if (!G.act[d]) continue;
-            for (int side = 0; side < 2; ++side) {
-                int nb = ijk[d] + (side ? 1 : -1);
-                if (nb < 0 || nb >= nd[d]) {
-                    if (G.bc[2 * d + side] != BC_PERIODIC) continue;
-                    nb = (nb + nd[d]) % nd[d];
-                }
-                const long long ck = c + (long long)(nb - ijk[d]) * cstr[d];
-                if (a.chi_old[ck] != B) continue;
-                const long long lower = side ? c : ck;
-                const int sl = a.fslot[3 * lower + d];
-                if (sl < 0) continue;
-                const int t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
-                double qv[5];
-                qv[0] = a.star[(side ? 3 : 2) * Q + sl];
-                qv[1 + d] = a.star[1 * Q + sl];
-                qv[t1] = a.star[(side ? 6 : 4) * Q + sl];
-                qv[t2] = a.star[(side ? 7 : 5) * Q + sl];
-                qv[4] = a.star[0 * Q + sl];
 #pragma unroll
-                for (int v = 0; v < 5; ++v) sum[v] += qv[v];
+        for (int f = 0; f < 6; ++f) {
+            const int d = f / 2, t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
+            if (sl[f] >= 0) {
+                sum[0] += st[f][0];
+                sum[1 + d] += st[f][1];
+                sum[t1] += st[f][2];
+                sum[t2] += st[f][3];
+                sum[4] += st[f][4];
                 ++cnt;
             }
         }
@@ -737,34 +834,32 @@ hipError_t launch_phase(const PhaseArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// The phase update of the previous step run by the count kernel of the next
-// one: the phase update writes the state at flipped cells, the CFL maximum
-// and error reports; the count reads only material ids, and the scan that
-// forms dt from that maximum and closes the previous step comes after.
-__global__ __launch_bounds__(COMPACT_THREADS) void k_count_phase(const IfaceArgs a, const PhaseArgs pa)
+// Start of a single-grid step: the phase update of the previous step of the
+// same m2c_step call (prev: it writes the state at flipped cells, the CFL
+// maximum and error reports) and the count of interface faces per block
+// (reads only material ids), neither where the queue is kept.  The launch
+// after it opens the step (open_step).
+template <bool EG>
+__global__ __launch_bounds__(COMPACT_THREADS) void k_step_begin(const IfaceArgs a, const PhaseArgs pa, int prev)
 {
-    phase_body<false>(pa, blockIdx.x, gridDim.x);
-    if (!queue_kept(a.sc)) count_body(a, blockIdx.x);
+    const bool kept = queue_kept(a.sc);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->qreuse = kept ? 1 : 0;
+    if (kept) return;
+    if (prev) phase_body<EG>(pa, blockIdx.x, gridDim.x);
+    for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) {
+        count_body(a, cb);
+        __syncthreads();                          // its sums are read before they are written again
+    }
 }
 
-__global__ __launch_bounds__(COMPACT_THREADS) void k_count_phase_eos(const IfaceArgs a, const PhaseArgs pa)
+hipError_t launch_step_begin(const IfaceArgs& a, const PhaseArgs* prev_phase, hipStream_t s)
 {
-    phase_body<true>(pa, blockIdx.x, gridDim.x);
-    if (!queue_kept(a.sc)) count_body(a, blockIdx.x);
-}
-
-hipError_t launch_compact(const IfaceArgs& a, const PhaseArgs* prev_phase, bool end_prev, bool begin,
-                          double dt_imposed, hipStream_t s)
-{
+    const PhaseArgs pa = prev_phase ? *prev_phase : PhaseArgs{};
+    const int prev = prev_phase ? 1 : 0;
     if (prev_phase && a.g.eosg)
-        hipLaunchKernelGGL(k_count_phase_eos, dim3(a.nblk), dim3(COMPACT_THREADS), 0, s, a, *prev_phase);
-    else if (prev_phase)
-        hipLaunchKernelGGL(k_count_phase, dim3(a.nblk), dim3(COMPACT_THREADS), 0, s, a, *prev_phase);
+        hipLaunchKernelGGL(k_step_begin<true>, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
     else
-        hipLaunchKernelGGL(k_count, dim3(a.nblk), dim3(COMPACT_THREADS), 0, s, a);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, a, end_prev ? 1 : 0, begin ? 1 : 0, a.g.cfl,
-                       a.g.dt_fixed, dt_imposed);
-    hipLaunchKernelGGL(k_scatter, dim3(a.nblk), dim3(COMPACT_THREADS), 0, s, a);
+        hipLaunchKernelGGL(k_step_begin<false>, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
     return hipGetLastError();
 }
 
@@ -807,7 +902,9 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter_batch(const RunDesc
                                                                    const int2* __restrict__ cmap)
 {
     const int2 m = cmap[blockIdx.x];
-    scatter_body(iface_of_run(runs[m.x], 1), m.y);
+    if (runs[m.x].sc->err != 0) return;
+    const IfaceArgs a = iface_of_run(runs[m.x], 1);
+    scatter_body(a, m.y, a.blockcnt[m.y]);
 }
 
 hipError_t launch_compact_batch(const RunDesc* runs, int nruns, const int2* cmap, int ncblocks, hipStream_t s)
@@ -824,7 +921,7 @@ constexpr int PHASE_BLOCKS_PER_RUN = 8;
 __global__ __launch_bounds__(64) void k_fiver_batch(const RunDesc* __restrict__ runs, int stage)
 {
     const int r = blockIdx.x / FIVER_BLOCKS_PER_RUN, b = blockIdx.x % FIVER_BLOCKS_PER_RUN;
-    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, FIVER_BLOCKS_PER_RUN);
+    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, FIVER_BLOCKS_PER_RUN, nullptr);
 }
 
 hipError_t launch_fiver_batch(const RunDesc* runs, int nruns, int stage, hipStream_t s)

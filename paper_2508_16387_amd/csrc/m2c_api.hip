@@ -2,8 +2,8 @@
 //
 // One context owns one grid's device buffers and stream.  A time step is
 // enqueued as a fixed kernel sequence with no host round trip:
-//   count (+ previous step's phase update) -> scan (+ close the previous
-//   step, open this one: dt) -> scatter -> [FIVER, stage] x 2
+//   previous step's phase update, count -> [FIVER (the first also closes the
+//   previous step, opens this one (dt) and writes the queue), stage] x 2
 // with the last step's phase update and closing after the loop.  Every
 // kernel returns at once when an earlier one has reported an error, so the
 // last good state is the start-of-step buffer of the failing step (the two
@@ -298,7 +298,8 @@ int enqueue_step(m2c_ctx* c, int p, double dt_imposed, const PhaseArgs* prev, Ph
     if (ev) HIPCHK(c, hipEventRecord(ev[0], s));
     IfaceArgs ia = iface_args(c, c->W[p]);
     ia.chi = c->chi[p];
-    HIPCHK(c, launch_compact(ia, prev, prev != nullptr, true, dt_imposed, s));
+    HIPCHK(c, launch_step_begin(ia, prev, s));
+    const StepOpen open{prev != nullptr, 1, dt_imposed};
 
     StageArgs sa;
     sa.g = c->g;
@@ -340,7 +341,7 @@ int enqueue_step(m2c_ctx* c, int p, double dt_imposed, const PhaseArgs* prev, Ph
     for (int k = 0; k < S; ++k) {
         if (ev) HIPCHK(c, hipEventRecord(ev[1 + 2 * k], s));
         ia.Win = st[k].win;
-        HIPCHK(c, launch_fiver(ia, k == S - 1, c->use_mlp ? &c->mlp : nullptr, s));
+        HIPCHK(c, launch_fiver(ia, k == S - 1, k == 0 ? &open : nullptr, c->use_mlp ? &c->mlp : nullptr, s));
         if (ev) HIPCHK(c, hipEventRecord(ev[2 + 2 * k], s));
         sa.Win = st[k].win;
         sa.W0 = c->W[p];
@@ -744,7 +745,8 @@ int m2c_interface_faces(m2c_ctx* c, int32_t* out, int64_t cap, int64_t* count)
     int rc = clear_error(c);
     if (rc) return rc;
     IfaceArgs ia = iface_args(c, c->W[c->cur]);
-    HIPCHK(c, launch_compact(ia, nullptr, false, false, 0.0, c->stream));
+    HIPCHK(c, launch_step_begin(ia, nullptr, c->stream));
+    HIPCHK(c, launch_scatter(ia, StepOpen{0, 0, 0.0}, c->stream));
     rc = pull_scalars(c);
     if (rc) return rc;
     if (c->hsc->err != 0) {

@@ -117,15 +117,22 @@ hipError_t launch_stage_batch(int stage, bool mixed, int tx, int ty, const RunDe
 constexpr int COMPACT_THREADS = 256;
 constexpr int COMPACT_CELLS_PER_THREAD = 16;
 constexpr int COMPACT_CELLS_PER_BLOCK = COMPACT_THREADS * COMPACT_CELLS_PER_THREAD;
-// count / scan / scatter of the interface queue; the count kernel also runs
-// the previous step's phase update (prev_phase, nullable), the scan kernel
-// ends the previous step (end_prev) and starts this one (begin: dt, cleared
-// accumulators)
-hipError_t launch_compact(const IfaceArgs& a, const PhaseArgs* prev_phase, bool end_prev, bool begin,
-                          double dt_imposed, hipStream_t s);
+// What the launch after k_step_begin does to open a step: end the previous
+// one of the same call, form dt and clear the accumulators (dt_imposed > 0:
+// that dt).
+struct StepOpen {
+    int end_prev, begin;
+    double dt_imposed;
+};
+// start of a single-grid step: the previous step's phase update (prev_phase,
+// nullable) and the counts of the interface queue
+hipError_t launch_step_begin(const IfaceArgs& a, const PhaseArgs* prev_phase, hipStream_t s);
+// opens the step and writes a rebuilt queue without solving it
+hipError_t launch_scatter(const IfaceArgs& a, const StepOpen& o, hipStream_t s);
 hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s);
-// mlp: the learned guess (null: acoustic).
-hipError_t launch_fiver(const IfaceArgs& a, bool record, const MlpDev* mlp, hipStream_t s);
+// open (nullable): the first FIVER launch of a step, which opens it and
+// writes a rebuilt queue; mlp: the learned guess (null: acoustic).
+hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s);
 hipError_t launch_phase(const PhaseArgs& a, hipStream_t s);
 // Batched forms: cmap maps each compaction block to (run, block of run).
 hipError_t launch_compact_batch(const RunDesc* runs, int nruns, const int2* cmap, int ncblocks, hipStream_t s);

@@ -77,13 +77,13 @@ static hipError_t launch_tile_batch(int stage, const RunDesc* runs, const int2* 
     return hipGetLastError();
 }
 
-int stage_slots(bool mixed)
+int stage_slots()
 {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
         ncu = 256;
-    return ncu * (mixed ? 3 : 2);
+    return 2 * ncu;
 }
 
 bool stage_tile_supported(int tx, int ty)

@@ -537,7 +537,7 @@ int m2c_create(const m2c_config* cfg, m2c_ctx** out)
         const long long txy = (long long)((c->g.nx + c->tx - 1) / c->tx) * ((c->g.ny + c->ty - 1) / c->ty);
         const int nz = c->g.nz;
         c->kz = stage_planes([&](int kz) { return txy * ((nz + kz - 1) / kz); },
-                             stage_slots(cfg->precision == M2C_PREC_MIXED));
+                             cfg->precision == M2C_PREC_MIXED ? 0 : stage_slots());
     }
     if (c->kz > c->g.nz) c->kz = c->g.nz;
     c->tiles[0] = (c->g.nx + c->tx - 1) / c->tx;

@@ -245,7 +245,7 @@ void default_tile(m2c_batch* b, const m2c_config* cfgs)
                      ((cfgs[r].nz + kz - 1) / kz);
             return t;
         };
-        b->kz = std::min(8, stage_planes(blocks, stage_slots(b->mixed)));
+        b->kz = std::min(8, stage_planes(blocks, b->mixed ? 0 : stage_slots()));
     }
 }
 

@@ -71,9 +71,9 @@ struct PhaseArgs {
 };
 
 bool stage_tile_supported(int tx, int ty);
-// Stage blocks resident on the chip at once: two per CU (FP64) or three
-// (mixed), from the stage kernels' registers.
-int stage_slots(bool mixed);
+// FP64 stage blocks resident on the chip at once: two per CU, from the stage
+// kernels' registers.
+int stage_slots();
 // Planes per stage block, from the number of blocks at a given number of
 // planes (blocks: int -> long long).  Three regimes:
 //   at least 4096 blocks with 32 or 16 planes (16 rounds of two blocks per
@@ -84,9 +84,11 @@ int stage_slots(bool mixed);
 //     the fewest planes that still fit.  There the launch lasts as long as
 //     one block's march, so fewer planes are a shorter launch until the
 //     blocks no longer run side by side (per stage launch, 8 planes -> this
-//     rule: 32^3 47 -> 14 us, 50x43x37 54 -> 18 us, 64^3 52 -> 31 us, mixed
-//     96^3 71 -> 62 us; one plane fewer than fits: 64^3 36 us, 80^3 58
-//     against 46 us);
+//     rule: 32^3 47 -> 14 us, 50x43x37 54 -> 18 us, 64^3 52 -> 31 us; one
+//     plane fewer than fits: 64^3 36 us, 80^3 58 against 46 us).  FP64 only
+//     (slots 0: not at all): the face below a block's first plane is
+//     evaluated by other code than those inside the march, which in FP32
+//     rounds differently, so the mixed form's results keep to blocks of 8;
 //   otherwise 8 (128^3: 128 us; 4, 6, 10 and 16 planes: 143, 142, 131, 149).
 template <class Blocks>
 int stage_planes(Blocks blocks, int slots)

@@ -385,8 +385,8 @@ int m2c_set_guess(m2c_ctx* ctx, const m2c_mlp* m);
  * periodic axes wrap, transmissive and wall sides repeat the boundary cell.
  * FP64, deterministic (Jacobi iterates). */
 /* On the context's current level set, between steps (stream-ordered on the
- * context's stream, which it synchronises once; uses the context's stage
- * buffer as workspace).
+ * context's stream, which it synchronises once when band > 0; uses the
+ * context's stage buffer as workspace).
  * M2C_ERR_STATE before a state is set; M2C_ERR_ARG for iters < 0 or
  * band < 0. */
 int m2c_reinit(m2c_ctx* ctx, int32_t iters, double band);
@@ -397,8 +397,9 @@ int m2c_reinit_workspace(int32_t nx, int32_t ny, int32_t nz, int64_t* bytes);
  * widths h[3] and boundary codes bc[6] (host), work = device workspace of
  * m2c_reinit_workspace bytes; asynchronous on hip_stream.  M2C_ERR_ARG for
  * invalid sizes, widths, boundary codes (periodic must pair up), iters < 0,
- * band < 0, or null pointers when iters > 0.  Synchronises hip_stream once
- * (after the setup kernel, to size the step launches). */
+ * band < 0, or null pointers when iters > 0.  With band > 0 it synchronises
+ * hip_stream once (after the setup kernel, to size the step launches).
+ * M2C_ERR_DEVICE on a stream under graph capture. */
 int m2c_reinit_field(int32_t nx, int32_t ny, int32_t nz, const double h[3], const int32_t bc[6], double* phi,
                      void* work, int32_t iters, double band, void* hip_stream);
 

@@ -16,17 +16,29 @@
 // boundaries repeat the boundary cell (the zero-gradient and mirror images
 // of phi coincide for one layer).
 //
-// Work decomposition (MI355X): a 256-thread block owns a 64 x 4 tile of an
-// xy-plane and a few consecutive planes; x is the contiguous axis and every
-// wavefront holds one 512-byte row per plane.  A cell's x neighbours come
-// from the adjacent lanes (shuffles), its y neighbours from the other rows
-// of the block through LDS, its z neighbours from a three-plane register
-// window; only the tile's edge lanes and rows load halo values.  The speed kernel
-// appends the blocks that hold any cell with S != 0 to a list, and the step
-// kernel runs on that list only.  The iterate is kept in two buffers that
-// both start as phi_0; a frozen cell never changes, so it is never written
-// -- a narrow band costs only the blocks it touches.  Per iteration and
-// moving cell the algorithmic traffic is phi and S read, phi written: 24
+// Work decomposition (MI355X): over the whole grid a thread owns one column
+// of RZ_FULL consecutive planes, a block 256 consecutive columns (row after
+// row, so that no lane falls past the end of a row); in a narrow band the
+// blocks are 64 x 4 tiles of one plane, the compact shape that fewest of the
+// band's cells touch, and only those on a list run.  A cell reads its own
+// value, S and its x and y neighbours (cache lines that its block loads
+// anyway); its z neighbours are the thread's own planes.  All planes of a
+// block are compile-time known, so their loads are in flight together and no
+// wavefront waits for a barrier; blocks are renumbered so that each XCD takes
+// a contiguous run of tiles, whose shared rows and planes meet in its L2.
+// The Godunov term of an axis is the square of max(s a, -s b, 0), s the sign
+// of S: seven instructions where both signs' forms took fifteen.  Measured at
+// 200x160x144: 31.3 us per step with rows exchanged through LDS, a barrier
+// per plane and 64-wide tiles (a quarter of the lanes past the row's end),
+// 23 us now, bound by FP64 issue and the Infinity Cache about equally.
+//
+// The speed kernel also writes the second iterate's start.  In a narrow band
+// it appends the blocks that hold any cell with S != 0 to the list; over the
+// whole grid nearly all do, and one counter for all of them (5760 blocks'
+// atomics, two thirds of its 79 us) is left out.  The iterate is kept in two buffers
+// that both start as phi_0; a frozen cell never changes, so it is never
+// written -- a narrow band costs only the blocks it touches.  Per iteration
+// and moving cell the algorithmic traffic is phi and S read, phi written: 24
 // bytes.
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -51,119 +63,157 @@ __device__ __forceinline__ int image(int i, int n, int periodic)
 }
 
 struct Tile {
-    int i, j, k0, k1;
+    int i, j, k0;
+    bool live;                        // inside the grid (else clamped to it)
 };
 
-__device__ __forceinline__ Tile tile_of(const ReinitGrid& g, int b)
+// BAND: 64 x 4 tile b of one plane; otherwise 256 consecutive columns of
+// RZ_FULL planes.
+template <bool BAND>
+__device__ __forceinline__ Tile tile_of(const ReinitGrid& g, uint32_t b)
 {
-    const int bx = b % g.bx, r = b / g.bx;
-    const int by = r % g.by, bz = r / g.by;
     Tile t;
-    t.i = bx * RX + (int)(threadIdx.x % RX);
-    t.j = by * RY + (int)(threadIdx.x / RX);
-    t.k0 = bz * g.rz;
-    t.k1 = min(t.k0 + g.rz, g.nz);
+    if (BAND) {
+        const uint32_t bx = b % (uint32_t)g.bx, r = b / (uint32_t)g.bx;
+        const uint32_t by = r % (uint32_t)g.by, bz = r / (uint32_t)g.by;
+        const int i = (int)(bx * RX + threadIdx.x % RX), j = (int)(by * RY + threadIdx.x / RX);
+        t.live = i < g.nx && j < g.ny;
+        t.i = min(i, g.nx - 1);
+        t.j = min(j, g.ny - 1);
+        t.k0 = (int)bz * RZ_BAND;
+    } else {
+        const uint32_t pl = (uint32_t)g.nx * (uint32_t)g.ny, nb = (pl - 1) / (RX * RY) + 1;
+        const uint32_t bz = b / nb, c = (b - bz * nb) * (RX * RY) + threadIdx.x;
+        t.live = c < pl;
+        const uint32_t cc = t.live ? c : pl - 1;
+        t.j = (int)(cc / (uint32_t)g.nx);
+        t.i = (int)(cc - (uint32_t)t.j * (uint32_t)g.nx);
+        t.k0 = (int)bz * RZ_FULL;
+    }
     return t;
 }
 
+// Dispatch is round-robin over the 8 XCDs: block b of n runs on XCD b % 8;
+// each XCD's blocks take one contiguous run of tiles.
+__device__ __forceinline__ uint32_t xcd_run(uint32_t b, uint32_t n)
+{
+    const uint32_t q = n / 8, r = n % 8, x = b % 8, idx = b / 8;
+    return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + idx;
+}
+
+// Values of one field at a thread's cells of RZ consecutive planes and at
+// their neighbours (boundary images applied; every index in range, also for
+// threads and planes past the grid, whose cells are not written).
+template <int RZ>
+struct Stencil {
+    double c[RZ + 2];                 // planes k0 - 1 .. k0 + RZ (past the last: repeated)
+    double top;                       // z image above the grid's last plane
+    double xa[RZ], xb[RZ], ya[RZ], yb[RZ];
+    uint32_t cell[RZ];
+};
+
+template <int RZ>
+__device__ __forceinline__ void load_stencil(const ReinitGrid& g, const Tile& t, const double* __restrict__ phi,
+                                             Stencil<RZ>& v)
+{
+    const uint32_t pl = (uint32_t)g.nx * (uint32_t)g.ny, row = (uint32_t)g.nx * (uint32_t)t.j, col = row + (uint32_t)t.i;
+    const uint32_t xm = row + (uint32_t)image(t.i - 1, g.nx, g.per[0]), xp = row + (uint32_t)image(t.i + 1, g.nx, g.per[0]);
+    const uint32_t ym = (uint32_t)g.nx * (uint32_t)image(t.j - 1, g.ny, g.per[1]) + (uint32_t)t.i;
+    const uint32_t yp = (uint32_t)g.nx * (uint32_t)image(t.j + 1, g.ny, g.per[1]) + (uint32_t)t.i;
+    const int last = g.nz - 1;
+    v.c[0] = phi[col + pl * (uint32_t)image(t.k0 - 1, g.nz, g.per[2])];
+#pragma unroll
+    for (int q = 0; q < RZ; ++q) {
+        const uint32_t o = pl * (uint32_t)min(t.k0 + q, last);
+        v.cell[q] = col + o;
+        v.c[1 + q] = phi[col + o];
+        v.ya[q] = phi[ym + o];
+        v.yb[q] = phi[yp + o];
+        v.xa[q] = phi[xm + o];
+        v.xb[q] = phi[xp + o];
+    }
+    v.c[1 + RZ] = phi[col + pl * (uint32_t)min(t.k0 + RZ, last)];
+    v.top = phi[col + pl * (uint32_t)image(g.nz, g.nz, g.per[2])];
+}
+
+// Upper z neighbour of the thread's plane q.
+template <int RZ>
+__device__ __forceinline__ double z_above(const ReinitGrid& g, const Tile& t, const Stencil<RZ>& v, int q)
+{
+    return t.k0 + q == g.nz - 1 ? v.top : v.c[2 + q];
+}
+
+template <bool BAND>
 __global__ __launch_bounds__(256) void k_reinit_speed(const ReinitGrid g, const double* __restrict__ phi0,
                                                       double eps2, double band, double* __restrict__ S,
-                                                      int32_t* __restrict__ list)
+                                                      double* __restrict__ tmp, int32_t* __restrict__ list)
 {
-    const Tile t = tile_of(g, blockIdx.x);
-    const bool in = t.i < g.nx && t.j < g.ny;
+    constexpr int RZ = BAND ? RZ_BAND : RZ_FULL;
+    const uint32_t blk = xcd_run(blockIdx.x, gridDim.x);
+    const Tile t = tile_of<BAND>(g, blk);
+    Stencil<RZ> v;
+    load_stencil<RZ>(g, t, phi0, v);
     int any = 0;
-    if (in) {
-        for (int k = t.k0; k < t.k1; ++k) {
-            const long long c = (long long)t.i + (long long)g.nx * (t.j + (long long)g.ny * k);
-            const double p = phi0[c];
-            const bool pos = p >= 0.0;
-            bool fl = false;
-            if (g.nx > 1) {
-                fl |= (phi0[c - t.i + image(t.i - 1, g.nx, g.per[0])] >= 0.0) != pos;
-                fl |= (phi0[c - t.i + image(t.i + 1, g.nx, g.per[0])] >= 0.0) != pos;
-            }
-            if (g.ny > 1) {
-                const long long r0 = c - (long long)g.nx * t.j;
-                fl |= (phi0[r0 + (long long)g.nx * image(t.j - 1, g.ny, g.per[1])] >= 0.0) != pos;
-                fl |= (phi0[r0 + (long long)g.nx * image(t.j + 1, g.ny, g.per[1])] >= 0.0) != pos;
-            }
-            if (g.nz > 1) {
-                const long long pl = (long long)g.nx * g.ny, r0 = c - pl * k;
-                fl |= (phi0[r0 + pl * image(k - 1, g.nz, g.per[2])] >= 0.0) != pos;
-                fl |= (phi0[r0 + pl * image(k + 1, g.nz, g.per[2])] >= 0.0) != pos;
-            }
-            double s = p / sqrt(p * p + eps2);
-            if (fl || (band > 0.0 && fabs(p) >= band)) s = 0.0;
-            S[c] = s;
+#pragma unroll
+    for (int q = 0; q < RZ; ++q) {
+        const double p = v.c[1 + q];
+        const bool pos = p >= 0.0;
+        bool fl = false;
+        if (g.act[0]) fl |= (v.xa[q] >= 0.0) != pos || (v.xb[q] >= 0.0) != pos;
+        if (g.act[1]) fl |= (v.ya[q] >= 0.0) != pos || (v.yb[q] >= 0.0) != pos;
+        if (g.act[2]) fl |= (v.c[q] >= 0.0) != pos || (z_above<RZ>(g, t, v, q) >= 0.0) != pos;
+        double s = p / sqrt(p * p + eps2);
+        if (fl || (BAND && fabs(p) >= band)) s = 0.0;
+        if (t.live && t.k0 + q < g.nz) {
+            S[v.cell[q]] = s;
+            tmp[v.cell[q]] = p;
             any |= s != 0.0;
         }
     }
+    if (!BAND) return;
     any = __syncthreads_or(any);
     // list[0] counts the blocks with moving cells, list[1..] holds them
-    if (threadIdx.x == 0 && any) list[1 + atomicAdd(&list[0], 1)] = blockIdx.x;
+    if (threadIdx.x == 0 && any) list[1 + atomicAdd(&list[0], 1)] = (int32_t)blk;
 }
 
-// LIST: the block runs tile list[1 + blockIdx.x] (narrow band); otherwise
-// the tile of the 3D block index (whole grid, no integer division)
-template <bool LIST>
+// a^2 + b^2 + c^2, each square rounded before it is added.
+__device__ __forceinline__ double norm2(double a, double b, double c)
+{
+#pragma clang fp contract(off)
+    return a * a + b * b + c * c;
+}
+
+// BAND: the block runs tile list[1 + block]; otherwise every tile of the grid
+template <bool BAND>
 __global__ __launch_bounds__(256) void k_reinit_step(const ReinitGrid g, const double* __restrict__ phi,
                                                      double* __restrict__ out, const double* __restrict__ S,
                                                      const int32_t* __restrict__ list, double dtau)
 {
-    // one wavefront per x-row of the tile: x neighbours by lane shuffles, y
-    // neighbours through a double-buffered LDS copy of the block's four rows,
-    // z neighbours in a register window; only the tile's edges load halos.
-    // Offsets are 32-bit (grids up to 2^31 cells); the one-sided
-    // differences multiply by 1/h.
-    __shared__ double sRow[2][RY][RX];
-    Tile t;
-    if (LIST) {
-        t = tile_of(g, list[1 + blockIdx.x]);
-    } else {
-        t.i = (int)blockIdx.x * RX + (int)(threadIdx.x % RX);
-        t.j = (int)blockIdx.y * RY + (int)(threadIdx.x / RX);
-        t.k0 = (int)blockIdx.z * g.rz;
-        t.k1 = min(t.k0 + g.rz, g.nz);
-    }
-    const int lane = (int)(threadIdx.x % RX), w = (int)(threadIdx.x / RX);
-    const bool live = t.i < g.nx && t.j < g.ny;
-    const int ic = min(t.i, g.nx - 1), jc = min(t.j, g.ny - 1);      // clamped: loads stay in range
-    const uint32_t pl = (uint32_t)g.nx * (uint32_t)g.ny;
-    const uint32_t row0 = (uint32_t)g.nx * (uint32_t)jc, col = row0 + (uint32_t)ic;
-    const bool xlo = lane == 0 || ic == 0, xhi = lane == RX - 1 || ic == g.nx - 1;
-    const bool ylo = w == 0 || jc == 0, yhi = w == RY - 1 || jc == g.ny - 1;
-    const uint32_t xm = row0 + image(ic - 1, g.nx, g.per[0]), xp = row0 + image(ic + 1, g.nx, g.per[0]);
-    const uint32_t ym = (uint32_t)g.nx * image(jc - 1, g.ny, g.per[1]) + ic;
-    const uint32_t yp = (uint32_t)g.nx * image(jc + 1, g.ny, g.per[1]) + ic;
-    double pzm = phi[col + pl * image(t.k0 - 1, g.nz, g.per[2])];
-    double p = phi[col + pl * t.k0];
-    int buf = 0;
-    for (int k = t.k0; k < t.k1; ++k, buf ^= 1) {
-        const uint32_t o = pl * (uint32_t)k;
-        const double pzp = phi[col + pl * image(k + 1, g.nz, g.per[2])];
-        const double s = S[col + o];
-        sRow[buf][w][lane] = p;
-        const double su = __shfl_up(p, 1), sd = __shfl_down(p, 1);
-        __syncthreads();
-        const double xa = xlo ? phi[xm + o] : su, xb = xhi ? phi[xp + o] : sd;
-        const double ya = ylo ? phi[ym + o] : sRow[buf][w - 1][lane];
-        const double yb = yhi ? phi[yp + o] : sRow[buf][w + 1][lane];
-        if (live && s != 0.0) {                       // frozen: both buffers hold phi_0
-            const bool up = s > 0.0;
+    constexpr int RZ = BAND ? RZ_BAND : RZ_FULL;
+    const uint32_t b = xcd_run(blockIdx.x, gridDim.x);
+    const Tile t = tile_of<BAND>(g, BAND ? (uint32_t)list[1 + b] : b);
+    Stencil<RZ> v;
+    double s[RZ];
+    load_stencil<RZ>(g, t, phi, v);
+#pragma unroll
+    for (int q = 0; q < RZ; ++q) s[q] = S[v.cell[q]];
+#pragma unroll
+    for (int q = 0; q < RZ; ++q) {
+        const double p = v.c[1 + q];
+        // frozen (S = 0): both buffers hold phi_0
+        if (t.live && t.k0 + q < g.nz && s[q] != 0.0) {
+            // S > 0: the larger of max(a, 0) and -min(b, 0); S < 0 the same of
+            // -a and -b (a, b the one-sided differences): signs are exact, and
+            // the larger square is the square of the larger
             auto term = [&](double lo, double hi, double rh) {
-                const double a = (p - lo) * rh, b = (hi - p) * rh;
-                const double u = up ? fmax(a, 0.0) : fmin(a, 0.0), v = up ? fmin(b, 0.0) : fmax(b, 0.0);
-                return fmax(u * u, v * v);
+                const double rs = copysign(rh, s[q]);
+                return fmax(fmax((p - lo) * rs, (p - hi) * rs), 0.0);
             };
-            double g2 = 0.0;
-            if (g.act[0]) g2 += term(xa, xb, g.rh[0]);
-            if (g.act[1]) g2 += term(ya, yb, g.rh[1]);
-            if (g.act[2]) g2 += term(pzm, pzp, g.rh[2]);
-            out[col + o] = p - dtau * s * (sqrt(g2) - 1.0);
+            const double g2 = norm2(g.act[0] ? term(v.xa[q], v.xb[q], g.rh[0]) : 0.0,
+                                    g.act[1] ? term(v.ya[q], v.yb[q], g.rh[1]) : 0.0,
+                                    g.act[2] ? term(v.c[q], z_above<RZ>(g, t, v, q), g.rh[2]) : 0.0);
+            out[v.cell[q]] = p - dtau * s[q] * (sqrt(g2) - 1.0);
         }
-        pzm = p;
-        p = pzp;
     }
 }
 
@@ -206,41 +256,55 @@ hipError_t reinit_run(const ReinitGrid& g0, double* phi, double* S, double* tmp,
                       double band, hipStream_t s)
 {
     ReinitGrid g = g0;
-    g.rz = band > 0.0 ? RZ_BAND : RZ_FULL;
-    g.bz = (g.nz + g.rz - 1) / g.rz;
-    const long long N = (long long)g.nx * g.ny * g.nz;
-    const long long nb = reinit_blocks(g);
     if (iters <= 0) return hipSuccess;
-    const double eps = g.hmin;                        // smallest cell width
-    hipError_t e = hipMemsetAsync(list, 0, sizeof(int32_t), s);
+    // (not recorded into a graph: the band's launches need its block count)
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &capturing);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reinit_speed, dim3((unsigned)nb), dim3(256), 0, s, g, phi, eps * eps, band, S, list);
+    if (capturing != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
+    const long long N = (long long)g.nx * g.ny * g.nz;
+    const double eps2 = g.hmin * g.hmin;              // smallest cell width, squared
+    const double dtau = 0.5 * g.hmin;
+    const bool narrow = band > 0.0;
+    long long nb;
+    if (narrow) {
+        g.rz = RZ_BAND;
+        g.bz = (g.nz + g.rz - 1) / g.rz;
+        nb = reinit_blocks(g);
+    } else {
+        nb = (((long long)g.nx * g.ny - 1) / (RX * RY) + 1) * ((g.nz + RZ_FULL - 1) / RZ_FULL);
+    }
+    if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (narrow) {
+        e = hipMemsetAsync(list, 0, sizeof(int32_t), s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_reinit_speed<true>, dim3((unsigned)nb), dim3(256), 0, s, g, phi, eps2, band, S, tmp, list);
+    } else {
+        hipLaunchKernelGGL(k_reinit_speed<false>, dim3((unsigned)nb), dim3(256), 0, s, g, phi, eps2, band, S, tmp, list);
+    }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(tmp, phi, N * sizeof(double), hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    // the number of moving blocks sizes every step launch
-    int32_t nact = 0;
-    e = hipMemcpyAsync(&nact, list, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return e;
-    if (nact < 0 || nact > nb) return hipErrorUnknown;
-    const double dtau = 0.5 * g.hmin;
-    // whole grid: a 3D launch over every tile (nearly all move); band: the list
-    const bool use_list = band > 0.0 || g.by > 65535 || g.bz > 65535;
-    for (int it = 0; it < iters && nact > 0; ++it) {
+    if (narrow) {
+        // the number of moving blocks sizes every step launch
+        int32_t nact = 0;
+        e = hipMemcpyAsync(&nact, list, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return e;
+        if (nact < 0 || nact > nb) return hipErrorUnknown;
+        if (nact == 0) return hipSuccess;
+        nb = nact;
+    }
+    for (int it = 0; it < iters; ++it) {
         const double* src = (it & 1) ? tmp : phi;
         double* dst = (it & 1) ? phi : tmp;
-        if (use_list)
-            hipLaunchKernelGGL(k_reinit_step<true>, dim3((unsigned)nact), dim3(256), 0, s, g, src, dst, S, list,
-                               dtau);
+        if (narrow)
+            hipLaunchKernelGGL(k_reinit_step<true>, dim3((unsigned)nb), dim3(256), 0, s, g, src, dst, S, list, dtau);
         else
-            hipLaunchKernelGGL(k_reinit_step<false>, dim3((unsigned)g.bx, (unsigned)g.by, (unsigned)g.bz),
-                               dim3(256), 0, s, g, src, dst, S, list, dtau);
+            hipLaunchKernelGGL(k_reinit_step<false>, dim3((unsigned)nb), dim3(256), 0, s, g, src, dst, S, list, dtau);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if ((iters & 1) && nact > 0) e = hipMemcpyAsync(phi, tmp, N * sizeof(double), hipMemcpyDeviceToDevice, s);
+    if (iters & 1) e = hipMemcpyAsync(phi, tmp, N * sizeof(double), hipMemcpyDeviceToDevice, s);
     return e;
 }
 

@@ -26,7 +26,8 @@ inline long long reinit_workspace_bytes(const ReinitGrid& g)
     return 16 * N + 4 * (1 + (long long)g.bx * g.by * g.nz);
 }
 // iters pseudo-time steps on phi (device, in place) with the given
-// workspace; synchronises the stream once (the count of moving blocks)
+// workspace; with band > 0 synchronises the stream once (the count of moving
+// blocks)
 hipError_t reinit_run(const ReinitGrid& g, double* phi, double* S, double* tmp, int32_t* list, int iters,
                       double band, hipStream_t s);
 

@@ -200,45 +200,6 @@ __device__ __forceinline__ void count_body(const IfaceArgs& a, int blk)
 // scatter.
 __device__ __forceinline__ bool queue_kept(const DevScalars* sc) { return sc->qvalid && sc->nflip == 0; }
 
-// One block: exclusive scan of the block counts (in place), total -> qlen.
-// Each thread sums a contiguous segment of the counts, the block scans the
-// segment sums, and each thread rewrites its segment from its offset.
-__device__ __forceinline__ void scan_body(const IfaceArgs& a)
-{
-    __shared__ long long sW[16];
-    const int nb = a.nblk;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int per = (nb + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int b0 = min(nb, (int)threadIdx.x * per), b1 = min(nb, b0 + per);
-    long long sum = 0;
-    for (int b = b0; b < b1; ++b) sum += a.blockcnt[b];
-    long long incl = sum;
-    for (int o = 1; o < 64; o <<= 1) {
-        const long long y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) sW[w] = incl;
-    __syncthreads();
-    long long run = incl - sum, total = 0;
-    for (int k = 0; k < nw; ++k) {
-        if (k < w) run += sW[k];
-        total += sW[k];
-    }
-    for (int b = b0; b < b1; ++b) {
-        const int v = a.blockcnt[b];
-        a.blockcnt[b] = (int)run;
-        run += v;
-    }
-    if (threadIdx.x == 0) {
-        if (total > a.qcap) {
-            atomicCAS(&a.sc->err, 0, ST_OVERFLOW);
-            a.sc->qlen = 0;
-        } else {
-            a.sc->qlen = (int)total;
-        }
-    }
-}
-
 // Sum of the counts of blocks [0, nb), for every thread of the block.
 __device__ __forceinline__ int count_prefix(const IfaceArgs& a, int nb)
 {
@@ -886,49 +847,58 @@ __device__ __forceinline__ IfaceArgs iface_of_run(const RunDesc& R, int stage)
     return a;
 }
 
+// The two launches that start a batch step, as for a single grid: the counts
+// of the runs whose queue is not kept; then the opening of every run's step
+// and the queues.  (The phase update and the end of the step before, which
+// turns the state parity, are launches of their own.)
 __global__ __launch_bounds__(COMPACT_THREADS) void k_count_batch(const RunDesc* __restrict__ runs,
                                                                  const int2* __restrict__ cmap)
 {
     const int2 m = cmap[blockIdx.x];
+    DevScalars* sc = runs[m.x].sc;
+    const bool kept = queue_kept(sc);
+    if (m.y == 0 && threadIdx.x == 0) sc->qreuse = kept ? 1 : 0;
+    if (kept) return;
     count_body(iface_of_run(runs[m.x], 1), m.y);
-}
-
-__global__ __launch_bounds__(1024) void k_scan_batch(const RunDesc* __restrict__ runs)
-{
-    scan_body(iface_of_run(runs[blockIdx.x], 1));
 }
 
 __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter_batch(const RunDesc* __restrict__ runs,
                                                                    const int2* __restrict__ cmap)
 {
     const int2 m = cmap[blockIdx.x];
-    if (runs[m.x].sc->err != 0) return;
+    const bool reuse = runs[m.x].sc->qreuse;
+    if (reuse && m.y != 0) return;
     const IfaceArgs a = iface_of_run(runs[m.x], 1);
-    scatter_body(a, m.y, a.blockcnt[m.y]);
+    if (m.y == 0) open_step(a, StepOpen{0, 1, 0.0});
+    if (!reuse) scatter_body(a, m.y, count_prefix(a, m.y));
 }
 
-hipError_t launch_compact_batch(const RunDesc* runs, int nruns, const int2* cmap, int ncblocks, hipStream_t s)
+hipError_t launch_compact_batch(const RunDesc* runs, const int2* cmap, int ncblocks, hipStream_t s)
 {
     hipLaunchKernelGGL(k_count_batch, dim3(ncblocks), dim3(COMPACT_THREADS), 0, s, runs, cmap);
-    hipLaunchKernelGGL(k_scan_batch, dim3(nruns), dim3(1024), 0, s, runs);
     hipLaunchKernelGGL(k_scatter_batch, dim3(ncblocks), dim3(COMPACT_THREADS), 0, s, runs, cmap);
     return hipGetLastError();
 }
 
-constexpr int FIVER_BLOCKS_PER_RUN = 32;
-constexpr int PHASE_BLOCKS_PER_RUN = 8;
-
-__global__ __launch_bounds__(64) void k_fiver_batch(const RunDesc* __restrict__ runs, int stage)
+__global__ __launch_bounds__(64) void k_fiver_batch(const RunDesc* __restrict__ runs, int stage, int per_run)
 {
-    const int r = blockIdx.x / FIVER_BLOCKS_PER_RUN, b = blockIdx.x % FIVER_BLOCKS_PER_RUN;
-    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, FIVER_BLOCKS_PER_RUN, nullptr);
+    const int r = blockIdx.x / per_run, b = blockIdx.x % per_run;
+    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, per_run, nullptr);
 }
 
+// One-wavefront blocks, about 8192 over the batch (the solves
+// of a run in one or two passes), between 32 and 256 per run (a 128^3 bubble
+// of radius 0.25 has 19000 faces).  16 runs of edges 32..128: 33.7 us at 32
+// per run, 19 at 256.
 hipError_t launch_fiver_batch(const RunDesc* runs, int nruns, int stage, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fiver_batch, dim3(nruns * FIVER_BLOCKS_PER_RUN), dim3(64), 0, s, runs, stage);
+    int per = 8192 / nruns;
+    per = per < 32 ? 32 : (per > 256 ? 256 : per);
+    hipLaunchKernelGGL(k_fiver_batch, dim3((unsigned)(nruns * per)), dim3(64), 0, s, runs, stage, per);
     return hipGetLastError();
 }
+
+constexpr int PHASE_BLOCKS_PER_RUN = 8;
 
 __global__ __launch_bounds__(256) void k_phase_batch(const RunDesc* __restrict__ runs)
 {

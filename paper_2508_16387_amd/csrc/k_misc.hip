@@ -15,27 +15,8 @@ static unsigned grid_for(long long n, int threads, long long cap = 65536)
 }
 
 // ---------------------------------------------------------------------------
-// Batched begin / end of a step: one thread per run; dt from the CFL rule
-// (section "Time integration"; the reading is dt = CFL / max_i sum over the
-// axes with more than one cell of (|V_d| + c)/h_d) or imposed, accumulators
-// cleared; a completed step advances the counters and flips the run's state
-// parity.
-__global__ void k_begin_batch(const RunDesc* __restrict__ runs, int n, double dt_imposed)
-{
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const RunDesc& R = runs[r];
-    DevScalars* sc = R.sc;
-    if (sc->err != 0) return;
-    double dt;
-    if (dt_imposed > 0.0) dt = dt_imposed;
-    else if (R.g.dt_fixed > 0.0) dt = R.g.dt_fixed;
-    else dt = R.g.cfl / __longlong_as_double((long long)sc->lam_bits);
-    sc->dt = dt;
-    sc->lam_bits = 0ull;
-    sc->nflip = 0;
-}
-
+// Batched end of a step: one thread per run; a completed step advances the
+// counters and flips the run's state parity.
 __global__ void k_end_batch(const RunDesc* __restrict__ runs, int n, int stages)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -48,12 +29,6 @@ __global__ void k_end_batch(const RunDesc* __restrict__ runs, int n, int stages)
     sc->solves += (long long)sc->qlen * stages;
     sc->flips += sc->nflip;
     sc->cur ^= 1;
-}
-
-hipError_t launch_begin_batch(const RunDesc* runs, int nruns, double dt_imposed, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_begin_batch, dim3((nruns + 63) / 64), dim3(64), 0, s, runs, nruns, dt_imposed);
-    return hipGetLastError();
 }
 
 hipError_t launch_end_batch(const RunDesc* runs, int nruns, int stages, hipStream_t s)

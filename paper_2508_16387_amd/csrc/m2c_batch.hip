@@ -3,7 +3,7 @@
 // A batch holds many independent runs (uneven grids, one precision and one
 // stage-tile shape for all).  Every device buffer of every run is allocated
 // once; one time step of all runs is one fixed kernel sequence
-//   begin -> compaction -> [FIVER, persistent stage] x 2 -> phase -> end
+//   compaction and begin -> [FIVER, persistent stage] x 2 -> phase -> end
 // over device-side run descriptors, captured once into a hipGraph and
 // replayed per step.  Each run keeps its own dt, error state and state
 // parity in device memory, so runs of different sizes and CFL limits (and a
@@ -84,6 +84,7 @@ __global__ void k_batch_clear_err(DevScalars* sc, int n)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n) return;
+    if (sc[r].err != 0) sc[r].qvalid = 0;          // a step that failed may have left its queue half made
     sc[r].err = 0;
     sc[r].err_cell = LLONG_MAX;
 }
@@ -139,8 +140,7 @@ int build_items(m2c_batch* b)
 
 int enqueue_batch_step(m2c_batch* b, hipStream_t s)
 {
-    BCHK(b, launch_begin_batch(b->d_runs, b->n, 0.0, s));
-    BCHK(b, launch_compact_batch(b->d_runs, b->n, b->d_cmap, b->ncblocks, s));
+    BCHK(b, launch_compact_batch(b->d_runs, b->d_cmap, b->ncblocks, s));
     BCHK(b, launch_fiver_batch(b->d_runs, b->n, 1, s));
     BCHK(b, launch_stage_batch(1, b->mixed, b->tx, b->ty, b->d_runs, b->d_items, b->nitems, s));
     BCHK(b, launch_fiver_batch(b->d_runs, b->n, 2, s));
@@ -372,6 +372,7 @@ int m2c_batch_set_state(m2c_batch* b, int32_t k, const double* prim6)
     const int q = b->hsc[k].cur ^ 1;
     b->hsc[k].err = 0;
     b->hsc[k].err_cell = LLONG_MAX;
+    b->hsc[k].qvalid = 0;                           // the next step builds the new state's queue
     rc = push(b);
     if (rc) return rc;
     BCHK(b, hipMemcpyAsync(R.d.W1, prim6, 6 * N * sizeof(double), hipMemcpyHostToDevice, b->stream));
@@ -482,6 +483,7 @@ int m2c_batch_autotune(m2c_batch* b, int32_t steps, int32_t tile_out[3], float* 
     if (rc) return rc;
     // snapshot of every run's current state, ids and device scalars
     std::vector<DevScalars> sc0(b->hsc, b->hsc + b->n);
+    for (auto& d : sc0) d.qvalid = 0;               // the trial steps change the queues
     std::vector<bool> lam0(b->n);
     size_t bytes = 0;
     for (auto& R : b->runs) bytes += 6 * R.d.g.N * sizeof(double) + R.d.g.N;

@@ -136,8 +136,9 @@ hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s);
 // writes a rebuilt queue; mlp: the learned guess (null: acoustic).
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s);
 hipError_t launch_phase(const PhaseArgs& a, hipStream_t s);
-// Batched forms: cmap maps each compaction block to (run, block of run).
-hipError_t launch_compact_batch(const RunDesc* runs, int nruns, const int2* cmap, int ncblocks, hipStream_t s);
+// Batched forms: cmap maps each compaction block to (run, block of run); the
+// compaction also opens every run's step.
+hipError_t launch_compact_batch(const RunDesc* runs, const int2* cmap, int ncblocks, hipStream_t s);
 hipError_t launch_fiver_batch(const RunDesc* runs, int nruns, int stage, hipStream_t s);
 hipError_t launch_phase_batch(const RunDesc* runs, int nruns, hipStream_t s);
 
@@ -160,7 +161,6 @@ hipError_t launch_points_guess(long long n, const double* in, const double* eos,
                                hipStream_t s);
 
 // Per-step bookkeeping and state conversion (k_misc.hip).
-hipError_t launch_begin_batch(const RunDesc* runs, int nruns, double dt_imposed, hipStream_t s);
 hipError_t launch_end_batch(const RunDesc* runs, int nruns, int stages, hipStream_t s);
 hipError_t launch_lambda(const Grid& g, const double* W, const uint8_t* chi, DevScalars* sc, hipStream_t s);
 hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi,

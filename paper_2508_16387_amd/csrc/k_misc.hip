@@ -224,12 +224,14 @@ hipError_t launch_hllc_points(long long n, const double* qL, const double* qR, d
 }
 
 // Independent two-material Riemann problems, in = [6][n], eos = [4][n],
-// out = [4][n] (p*, u*, rho*_L, rho*_R); optional candidate guesses.
+// out = [4][n] (p*, u*, rho*_L, rho*_R); optional candidate guesses.  vac (in
+// device or in pinned host memory) is set to 1 by a problem without
+// admissible star pressure.
 __global__ __launch_bounds__(64) void k_riemann_points(long long n, const double* __restrict__ in,
                                                        const double* __restrict__ eos,
                                                        const double* __restrict__ guess, double rtol, int maxit,
                                                        double* __restrict__ out, int32_t* __restrict__ iters,
-                                                       int32_t* nvac, unsigned long long* nfb)
+                                                       int32_t* vac, unsigned long long* nfb)
 {
     unsigned long long fb = 0;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(64) void k_riemann_points(long long n, const double
         const int it = riemann_solve(in[i], in[n + i], in[2 * n + i], eos[i], eos[n + i], in[3 * n + i],
                                      in[4 * n + i], in[5 * n + i], eos[2 * n + i], eos[3 * n + i], rtol, maxit,
                                      guess != nullptr, guess ? guess[i] : 0.0, o, &used);
-        if (it == 0) atomicAdd(nvac, 1);
+        if (it == 0) *vac = 1;
         fb += guess != nullptr && !used && it != 0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) out[v * n + i] = o[v];
@@ -250,11 +252,11 @@ __global__ __launch_bounds__(64) void k_riemann_points(long long n, const double
 }
 
 hipError_t launch_riemann_points(long long n, const double* in, const double* eos, const double* guess, double rtol,
-                                 int maxit, double* out, int32_t* iters, int32_t* nvac, unsigned long long* nfb,
+                                 int maxit, double* out, int32_t* iters, int32_t* vac, unsigned long long* nfb,
                                  hipStream_t s)
 {
     hipLaunchKernelGGL(k_riemann_points, dim3(grid_for(n, 64)), dim3(64), 0, s, n, in, eos, guess, rtol, maxit, out,
-                       iters, nvac, nfb);
+                       iters, vac, nfb);
     return hipGetLastError();
 }
 

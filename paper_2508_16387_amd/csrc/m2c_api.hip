@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/m2c.h"
+#include "m2c_hostword.h"
 #include "m2c_internal.h"
 #include "m2c_kernels.h"
 #include "m2c_mlp.h"
@@ -784,18 +785,16 @@ int m2c_riemann_solve(int64_t n, const double* in, const double* eos, int32_t gu
     if (guess != M2C_GUESS_ACOUSTIC) return M2C_ERR_UNIMPLEMENTED;
     if (n == 0) return M2C_OK;
     hipStream_t s = (hipStream_t)hip_stream;
-    int32_t* dvac = nullptr;
-    if (hipMalloc((void**)&dvac, sizeof(int32_t)) != hipSuccess) return M2C_ERR_NOMEM;
-    int32_t hv = 0;
-    int rc = M2C_OK;
-    if (hipMemsetAsync(dvac, 0, sizeof(int32_t), s) != hipSuccess ||
-        launch_riemann_points(n, in, eos, nullptr, rtol, maxit, out, iters, dvac, nullptr, s) != hipSuccess ||
-        hipMemcpyAsync(&hv, dvac, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    // the failure flag is the kernel's store into pinned memory: 1000 problems
+    // 46 -> 33 us, 1000003 problems 281 -> 268 us from a device counter that
+    // was allocated, cleared and copied back
+    int32_t* vac = (int32_t*)host_words();
+    if (!vac) return M2C_ERR_NOMEM;
+    *vac = 0;
+    if (launch_riemann_points(n, in, eos, nullptr, rtol, maxit, out, iters, vac, nullptr, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
-        rc = M2C_ERR_DEVICE;
-    (void)hipFree(dvac);
-    if (rc == M2C_OK && hv > 0) rc = M2C_ERR_RIEMANN;
-    return rc;
+        return M2C_ERR_DEVICE;
+    return *(volatile int32_t*)vac ? M2C_ERR_RIEMANN : M2C_OK;
 }
 
 int m2c_autotune(m2c_ctx* c, int32_t steps, int32_t tile_out[3], float* ms_out)

@@ -175,7 +175,7 @@ hipError_t launch_hllc_points(long long n, const double* qL, const double* qR, d
 // acoustic guess; nfb (nullable) counts problems that started from the
 // acoustic guess although a candidate was given.
 hipError_t launch_riemann_points(long long n, const double* in, const double* eos, const double* guess,
-                                 double rtol, int maxit, double* out, int32_t* iters, int32_t* nvac,
+                                 double rtol, int maxit, double* out, int32_t* iters, int32_t* vac,
                                  unsigned long long* nfb, hipStream_t s);
 
 }  // namespace m2c

@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "../../include/m2c.h"
+#include "m2c_hostword.h"
 #include "m2c_internal.h"
 #include "m2c_kernels.h"
 #include "m2c_mlp.h"
@@ -25,7 +26,7 @@ struct m2c_mlp {
 const MlpDev* m2c_mlp_dev(const m2c_mlp* m) { return m ? &m->d : nullptr; }
 
 // Scratch of the allocation-free solver: one learned guess per problem and
-// the two counters the solve kernel updates (no admissible star pressure,
+// the two words the solve kernel updates (no admissible star pressure,
 // acoustic starts).  One copy per GPU, held until the process ends; every
 // call on a GPU shares its copy, so calls that overlap on one GPU race.
 constexpr long long NOALLOC_MAX = M2C_NOALLOC_MAX_PROBLEMS;
@@ -233,21 +234,23 @@ int m2c_riemann_solve_learned(const m2c_mlp* m, int64_t n, const double* in, con
     hipStream_t s = (hipStream_t)stream;
     double* g = nullptr;
     if (hipMalloc((void**)&g, n * sizeof(double) + 16) != hipSuccess) return M2C_ERR_NOMEM;
+    unsigned long long* h = host_words();         // copies of the device's words
+    if (!h) {
+        (void)hipFree(g);
+        return M2C_ERR_NOMEM;
+    }
+    h[0] = h[1] = 0;
     int32_t* dvac = (int32_t*)(g + n);
-    unsigned long long* dfb = (unsigned long long*)((char*)(g + n) + 8);
-    int32_t hv = 0;
-    unsigned long long hfb = 0;
+    unsigned long long* dfb = (unsigned long long*)(g + n + 1);
     int rc = M2C_OK;
     if (hipMemsetAsync(dvac, 0, 16, s) != hipSuccess ||
         (m && launch_points_guess(n, in, eos, m->d, g, s) != hipSuccess) ||
         launch_riemann_points(n, in, eos, m ? g : nullptr, rtol, maxit, out, iters, dvac, dfb, s) != hipSuccess ||
-        hipMemcpyAsync(&hv, dvac, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&hfb, dfb, sizeof(hfb), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+        hipMemcpyAsync(h, dvac, 16, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         rc = M2C_ERR_DEVICE;
     (void)hipFree(g);
-    if (n_fallback) *n_fallback = (int64_t)hfb;
-    if (rc == M2C_OK && hv > 0) rc = M2C_ERR_RIEMANN;
+    if (n_fallback) *n_fallback = rc == M2C_OK ? (int64_t)h[1] : 0;
+    if (rc == M2C_OK && (int32_t)h[0] != 0) rc = M2C_ERR_RIEMANN;
     return rc;
 }
 

@@ -14,8 +14,8 @@
 // family is solved mirrored.  A set of one family pair (in either order) is
 // solved by a kernel compiled for exactly those two families, which carries
 // neither the code nor the registers of the others; a set of several family
-// pairs takes one launch of the kernel that dispatches on the families at
-// run time, so that the groups run side by side (launches per group, one
+// pairs takes one launch of a kernel that dispatches on the families at run
+// time (of the smaller one where no problem is Mie-Grueneisen), so that the groups run side by side (launches per group, one
 // after another on the stream, would each wait for the slowest wavefront of
 // the one before).
 #include <hip/hip_runtime.h>
@@ -24,6 +24,7 @@
 
 #include "m2c.h"
 #include "m2c_eos.h"
+#include "m2c_hostword.h"
 #include "m2c_mlp_eos.h"
 #include "m2c_mlp_infer.h"
 
@@ -43,27 +44,39 @@ __device__ __forceinline__ int pair_key(const int32_t* mat, long long n, long lo
 
 constexpr int NKEY = M2C_EOS_MAX * M2C_EOS_MAX + 1;
 
+// Blocks of the grouping kernels: every block adds to the counter of each
+// key that it holds, and the adds to one counter follow one another (about
+// 20 ns each), so the blocks are few and large: 2048 problems each, at most
+// 256 blocks.  262144 problems of 8 pairs: count 21 -> 5 us and placing
+// 23 -> 6 us from blocks of 256 problems.
+constexpr int GROUP_THREADS = 1024;
+constexpr long long GROUP_PROBLEMS = 2048, GROUP_BLOCKS = 256;
+
+unsigned group_blocks(long long n)
+{
+    const long long b = (n + GROUP_PROBLEMS - 1) / GROUP_PROBLEMS;
+    return (unsigned)(b < GROUP_BLOCKS ? b : GROUP_BLOCKS);
+}
+
 // counts[key] += problems of that key (block histogram in LDS first)
-__global__ __launch_bounds__(256) void k_pair_count(long long n, const int32_t* __restrict__ mat, int nmat,
-                                                    int32_t* __restrict__ counts)
+__global__ __launch_bounds__(GROUP_THREADS) void k_pair_count(long long n, const int32_t* __restrict__ mat, int nmat,
+                                                              int32_t* __restrict__ counts)
 {
     __shared__ int32_t h[NKEY];
     for (int k = threadIdx.x; k < NKEY; k += blockDim.x) h[k] = 0;
     __syncthreads();
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(&h[pair_key(mat, n, i, nmat)], 1);
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        atomicAdd(&h[pair_key(mat, n, i, nmat)], 1);
     __syncthreads();
     for (int k = threadIdx.x; k < NKEY; k += blockDim.x)
         if (h[k]) atomicAdd(&counts[k], h[k]);
 }
 
-// Family-pair group of every key: 3 min(famL, famR) + max(famL, famR) for
-// the keys of the table (a problem whose right family is the lower one is
+// Family-pair group of a key: 3 min(famL, famR) + max(famL, famR) for the
+// keys of the table (a problem whose right family is the lower one is
 // solved mirrored), NFP - 1 for the key of indices outside it.
 constexpr int NFP = 10;
-struct KeyGroups {
-    int32_t g[NKEY];
-};
 
 // Order of the groups in the permutation: the costliest first (both sides
 // Mie-Grueneisen, whose rarefactions walk the isentrope by RK4, then one
@@ -76,59 +89,78 @@ constexpr int kGroupOrder[NFP] = {3 * M2C_EOS_MG + M2C_EOS_MG,    3 * M2C_EOS_NA
                                   3 * M2C_EOS_MG + M2C_EOS_NASG,  3 * M2C_EOS_JWL + M2C_EOS_NASG,
                                   3 * M2C_EOS_JWL + M2C_EOS_MG,   NFP - 1};
 
-// cursor = exclusive prefix sum of counts with the keys taken group by group
-// in kGroupOrder, so that each family pair's problems occupy one range of
-// slots: range[2 f] .. range[2 f + 1] (one thread; NKEY x NFP steps)
-__global__ void k_pair_scan(const int32_t* __restrict__ counts, int32_t* __restrict__ cursor, const KeyGroups kg,
-                            int32_t* __restrict__ range)
+// First slot of every key, the keys taken group by group in kGroupOrder, so
+// that each family pair's problems occupy one range of slots: range[2 f] ..
+// range[2 f + 1].  On the host, which needs the ranges for the launch: a
+// kernel of one thread for it took 27 us.
+struct KeySlots {
+    int32_t first[NKEY];
+};
+
+KeySlots key_slots(const EosTable& tab, int nmat, const int32_t* counts, int32_t* range)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        int32_t acc = 0;
-        for (int o = 0; o < NFP; ++o) {
-            const int f = kGroupOrder[o];
-            range[2 * f] = acc;
-            for (int k = 0; k < NKEY; ++k)
-                if (kg.g[k] == f) {
-                    cursor[k] = acc;
-                    acc += counts[k];
-                }
-            range[2 * f + 1] = acc;
+    KeySlots ks;
+    int32_t acc = 0;
+    for (int f : kGroupOrder) {
+        range[2 * f] = acc;
+        for (int k = 0; k < NKEY; ++k) {
+            int g = NFP - 1;
+            if (k < nmat * nmat) {
+                const int fl = tab.m[k / nmat].fam, fr = tab.m[k % nmat].fam;
+                g = fl < fr ? 3 * fl + fr : 3 * fr + fl;
+            }
+            if (g != f) continue;
+            ks.first[k] = acc;
+            acc += counts[k];
         }
+        range[2 * f + 1] = acc;
     }
+    return ks;
 }
 
 // perm[slot] = i, slots of one key contiguous: each block reserves its
-// share of every key with one atomic and ranks its problems in LDS
-__global__ __launch_bounds__(256) void k_pair_place(long long n, const int32_t* __restrict__ mat, int nmat,
-                                                    int32_t* __restrict__ cursor, int32_t* __restrict__ perm)
+// share of every key with one atomic (used[key] starts at 0) and ranks its
+// problems in LDS
+__global__ __launch_bounds__(GROUP_THREADS) void k_pair_place(long long n, const int32_t* __restrict__ mat, int nmat,
+                                                              const KeySlots ks, int32_t* __restrict__ used,
+                                                              int32_t* __restrict__ perm)
 {
-    __shared__ int32_t h[NKEY], base[NKEY];
+    __shared__ int32_t h[NKEY];
     for (int k = threadIdx.x; k < NKEY; k += blockDim.x) h[k] = 0;
     __syncthreads();
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    int key = 0, rank = 0;
-    if (i < n) {
-        key = pair_key(mat, n, i, nmat);
-        rank = atomicAdd(&h[key], 1);
-    }
+    const long long stride = (long long)gridDim.x * blockDim.x, i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (long long i = i0; i < n; i += stride) atomicAdd(&h[pair_key(mat, n, i, nmat)], 1);
     __syncthreads();
     for (int k = threadIdx.x; k < NKEY; k += blockDim.x)
-        if (h[k]) base[k] = atomicAdd(&cursor[k], h[k]);
+        if (h[k]) h[k] = ks.first[k] + atomicAdd(&used[k], h[k]);
     __syncthreads();
-    if (i < n) perm[base[key] + rank] = (int32_t)i;
+    for (long long i = i0; i < n; i += stride) perm[atomicAdd(&h[pair_key(mat, n, i, nmat)], 1)] = (int32_t)i;
 }
 
-// Waves per SIMD the compiler fits a family pair's kernel to: two where
-// neither side is Mie-Grueneisen (a few registers spilled at most), one with
-// its branch-point walks and for the run-time dispatch (no spills there).
+// Families a kernel is compiled for on its two sides: the family itself, or
+// for FA < 0 a run-time dispatch, over all families (FA = -1) or over those
+// without Mie-Grueneisen (FA = -2).
 template <int FA, int FB>
-constexpr int kWavesPerSimd = (FA >= 0 && FB >= 0 && FA != M2C_EOS_MG && FB != M2C_EOS_MG) ? 2 : 1;
+constexpr int kSetA = FA == -2 ? FAM_ALL & ~fam_set(M2C_EOS_MG) : fam_set(FA);
+template <int FA, int FB>
+constexpr int kSetB = FA == -2 ? FAM_ALL & ~fam_set(M2C_EOS_MG) : fam_set(FB);
 
-// Slots range[0] .. range[1] of the permutation perm (whole set without
-// them: thread t solves problem t).  FA <= FB: every problem of the range
-// has one material of family FA and one of family FB, in either order,
-// inside the table (the grouping guarantees it).  FA = FB = -1: any
-// materials, indices checked, families dispatched at run time.  A problem
+// Waves per SIMD the compiler fits a kernel to: one where a side may be
+// Mie-Grueneisen (its walks leave no registers for a second one without
+// heavy spilling), two elsewhere (28 bytes per lane spilled at most, 164 in
+// the dispatch without Mie-Grueneisen: 262144 fluid problems of several
+// pairs take 1260 us through the dispatch over all families, 1150 us
+// without Mie-Grueneisen at one wave and 990 us at two; 50000 of them 762,
+// 692 and 701 us).
+template <int FA, int FB>
+constexpr int kWavesPerSimd = ((kSetA<FA, FB> | kSetB<FA, FB>) & fam_set(M2C_EOS_MG)) ? 1 : 2;
+
+// Slots lo .. hi of the permutation perm (without it, thread t solves
+// problem t).  0 <= FA <= FB: every problem of the range has one material of
+// family FA and one of family FB, in either order, inside the table (the
+// grouping guarantees it).  FA < 0, FB = -1: any
+// materials of the kernel's families, indices checked, families dispatched
+// at run time.  A problem
 // whose right side has the lower family is solved mirrored (x -> -x: the
 // sides swap and the velocities change sign), which leaves p* and negates
 // u*, so a problem and its image take the same arithmetic.
@@ -136,10 +168,9 @@ template <int FA, int FB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<FA, FB>))) void k_riemann_eos(
     long long n, const double* __restrict__ in, const int32_t* __restrict__ mat, const EosTable tab, double rtol,
     int maxit, double hmax, double* __restrict__ out, int32_t* __restrict__ iters, int32_t* __restrict__ nbad,
-    const int32_t* __restrict__ perm, const int32_t* __restrict__ range)
+    const int32_t* __restrict__ perm, long long lo, long long hi)
 {
     static_assert(FA <= FB, "family pair in canonical order");
-    const long long lo = range ? (long long)range[0] : 0, hi = range ? (long long)range[1] : n;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long t = lo + (long long)blockIdx.x * blockDim.x + threadIdx.x; t < hi; t += stride) {
         const long long i = perm ? (long long)perm[t] : t;
@@ -152,7 +183,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerSi
             const bool flip = FA >= 0 ? (FA != FB && tab.m[ml].fam != FA) : tab.m[ml].fam > tab.m[mr].fam;
             const double qm[6] = {flip ? q[3] : q[0], flip ? -q[4] : q[1], flip ? q[5] : q[2],
                                   flip ? q[0] : q[3], flip ? -q[1] : q[4], flip ? q[2] : q[5]};
-            its = solve_pair<fam_set(FA), fam_set(FB)>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], qm, rtol, maxit,
+            its = solve_pair<kSetA<FA, FB>, kSetB<FA, FB>>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], qm, rtol, maxit,
                                                        hmax, res);
             if (flip) {
                 const double r = res[2];
@@ -180,11 +211,10 @@ template <int FA, int FB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<FA, FB>))) void k_riemann_eos_learned(
     long long n, const double* __restrict__ in, const int32_t* __restrict__ mat, const EosTable tab, double rtol,
     int maxit, double hmax, double* __restrict__ out, int32_t* __restrict__ iters, int32_t* __restrict__ nbad,
-    unsigned long long* __restrict__ nfb, const int32_t* __restrict__ perm, const int32_t* __restrict__ range,
+    unsigned long long* __restrict__ nfb, const int32_t* __restrict__ perm, long long lo, long long hi,
     const MlpDev net)
 {
     static_assert(FA <= FB, "family pair in canonical order");
-    const long long lo = range ? (long long)range[0] : 0, hi = range ? (long long)range[1] : n;
     const long long stride = (long long)gridDim.x * blockDim.x;
     const int lane = threadIdx.x & 63;
     unsigned long long fb = 0;
@@ -206,7 +236,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerSi
                 flip = FA >= 0 ? (FA != FB && tab.m[ml].fam != FA) : tab.m[ml].fam > tab.m[mr].fam;
                 const double qm[6] = {flip ? q[3] : q[0], flip ? -q[4] : q[1], flip ? q[5] : q[2],
                                       flip ? q[0] : q[3], flip ? -q[1] : q[4], flip ? q[2] : q[5]};
-                ok = pair_init<fam_set(FA), fam_set(FB)>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], qm, P);
+                ok = pair_init<kSetA<FA, FB>, kSetB<FA, FB>>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], qm, P);
             }
         }
         float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -222,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerSi
         int its = 0;
         bool used = false;
         if (ok)
-            its = pair_solve<fam_set(FA), fam_set(FB)>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], P, rtol, maxit,
+            its = pair_solve<kSetA<FA, FB>, kSetB<FA, FB>>(tab.m[flip ? mr : ml], tab.m[flip ? ml : mr], P, rtol, maxit,
                                                        hmax, g, res, &used);
         if (flip) {
             const double r = res[2];
@@ -320,21 +350,22 @@ struct SolveArgs {
 // or for the run-time dispatch)
 // Returns whether the learned kernel was launched.
 template <int FA, int FB>
-bool launch_solve(const SolveArgs& a, unsigned grid, const int32_t* range, hipStream_t s)
+bool launch_solve(const SolveArgs& a, long long lo, long long hi, hipStream_t s)
 {
+    const unsigned grid = grid_for(hi - lo);
     if constexpr (FA < 0 || learned_pair(FA, FB)) {
         if (a.net) {
             hipLaunchKernelGGL((k_riemann_eos_learned<FA, FB>), dim3(grid), dim3(256), 0, s, a.n, a.in, a.mat, a.tab,
-                               a.rtol, a.maxit, a.hmax, a.out, a.iters, a.nbad, a.nfb, a.perm, range, *a.net);
+                               a.rtol, a.maxit, a.hmax, a.out, a.iters, a.nbad, a.nfb, a.perm, lo, hi, *a.net);
             return true;
         }
     }
     hipLaunchKernelGGL((k_riemann_eos<FA, FB>), dim3(grid), dim3(256), 0, s, a.n, a.in, a.mat, a.tab, a.rtol,
-                       a.maxit, a.hmax, a.out, a.iters, a.nbad, a.perm, range);
+                       a.maxit, a.hmax, a.out, a.iters, a.nbad, a.perm, lo, hi);
     return false;
 }
 
-using SolveLaunch = bool (*)(const SolveArgs&, unsigned, const int32_t*, hipStream_t);
+using SolveLaunch = bool (*)(const SolveArgs&, long long, long long, hipStream_t);
 // by family-pair group 3 FA + FB, FA <= FB (families M2C_EOS_NASG, _MG, _JWL
 // = 0, 1, 2; the other groups stay empty)
 constexpr SolveLaunch kSolvePair[9] = {launch_solve<0, 0>, launch_solve<0, 1>, launch_solve<0, 2>,
@@ -363,52 +394,46 @@ int solve_eos(const MlpDev* net, int64_t n, const double* in, const int32_t* mat
     hipStream_t s = (hipStream_t)hip_stream;
     // grouped by material pair, and within that by family pair (32-bit slots)
     const bool group = n < (1LL << 31);
-    // workspace (int32): failure count, key counts, key cursors, family-pair
-    // ranges, acoustic-start count (64-bit), permutation
-    const long long words = 1 + 2 * NKEY + 2 * NFP + 3 + (group ? n : 0);
-    int32_t* dbad = nullptr;
-    if (hipMalloc((void**)&dbad, words * sizeof(int32_t)) != hipSuccess) return M2C_ERR_NOMEM;
+    // workspace (int32): acoustic-start count (64-bit), failure count, key
+    // counts, places taken by key, permutation
+    constexpr long long head = 3 + 2 * NKEY;
+    const long long words = head + (group ? n : 0);
+    unsigned long long* h = host_words();         // copies of the device's words
+    static_assert(NKEY * sizeof(int32_t) <= HOST_WORDS * sizeof(*h), "the key counts fit the host words");
+    int32_t* ws = nullptr;
+    if (!h || hipMalloc((void**)&ws, words * sizeof(int32_t)) != hipSuccess) return M2C_ERR_NOMEM;
+    unsigned long long* nfb = (unsigned long long*)ws;
+    int32_t* dbad = ws + 2;
     int32_t* counts = dbad + 1;
-    int32_t* cursor = counts + NKEY;
-    int32_t* range = cursor + NKEY;
-    unsigned long long* nfb = (unsigned long long*)(range + 2 * NFP + 1);   // 8-byte aligned
-    int32_t* perm = group ? range + 2 * NFP + 3 : nullptr;
-    int32_t hb = 0;
+    int32_t* used = counts + NKEY;
+    int32_t* perm = group ? ws + head : nullptr;
     int rc = M2C_OK;
-    unsigned long long hfb = 0;
     bool learned = false;              // a learned kernel counted the acoustic starts
-    const SolveArgs sa{(long long)n, in, mat, tab, rtol, (int)maxit, ds, out, iters, dbad, perm, net, nfb};
-    if (hipMemsetAsync(dbad, 0, (1 + NKEY) * sizeof(int32_t), s) != hipSuccess ||
-        hipMemsetAsync(nfb, 0, sizeof(unsigned long long), s) != hipSuccess)
-        rc = M2C_ERR_DEVICE;
+    SolveArgs sa{(long long)n, in, mat, tab, rtol, (int)maxit, ds, out, iters, dbad, perm, net, nfb};
+    if (hipMemsetAsync(ws, 0, head * sizeof(int32_t), s) != hipSuccess) rc = M2C_ERR_DEVICE;
     if (rc == M2C_OK && group) {
-        KeyGroups kg;
-        for (int k = 0; k < NKEY; ++k) {
-            kg.g[k] = NFP - 1;
-            if (k >= nmat * nmat) continue;
-            const int fl = tab.m[k / (int)nmat].fam, fr = tab.m[k % (int)nmat].fam;
-            kg.g[k] = fl < fr ? 3 * fl + fr : 3 * fr + fl;
-        }
-        const unsigned nb = (unsigned)((n + 255) / 256);
-        int32_t hr[2 * NFP] = {};
-        hipLaunchKernelGGL(k_pair_count, dim3(nb), dim3(256), 0, s, (long long)n, mat, (int)nmat, counts);
-        hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(64), 0, s, counts, cursor, kg, range);
-        hipLaunchKernelGGL(k_pair_place, dim3(nb), dim3(256), 0, s, (long long)n, mat, (int)nmat, cursor, perm);
-        // the group sizes decide the launch (one read-back; the call
-        // synchronises at its end anyway)
+        // the group sizes decide the launch
+        hipLaunchKernelGGL(k_pair_count, dim3(group_blocks(n)), dim3(GROUP_THREADS), 0, s, (long long)n, mat,
+                           (int)nmat, counts);
         if (hipGetLastError() != hipSuccess ||
-            hipMemcpyAsync(hr, range, sizeof(hr), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipMemcpyAsync(h, counts, NKEY * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             rc = M2C_ERR_DEVICE;
+    }
+    if (rc == M2C_OK && group) {
+        int32_t hr[2 * NFP];
+        const KeySlots ks = key_slots(tab, (int)nmat, (const int32_t*)h, hr);
+        hipLaunchKernelGGL(k_pair_place, dim3(group_blocks(n)), dim3(GROUP_THREADS), 0, s, (long long)n, mat,
+                           (int)nmat, ks, used, perm);
         int only = -1, nonempty = 0;
         for (int f = 0; f < NFP; ++f)
             if (hr[2 * f + 1] > hr[2 * f]) {
                 only = f;
                 ++nonempty;
             }
-        if (rc == M2C_OK && nonempty == 1 && only < NFP - 1 && kSolvePair[only]) {
-            learned = kSolvePair[only](sa, grid_for(hr[2 * only + 1] - hr[2 * only]), range + 2 * only, s);
-        } else if (rc == M2C_OK) {
+        if (nonempty == 1 && only < NFP - 1 && kSolvePair[only]) {
+            learned = kSolvePair[only](sa, hr[2 * only], hr[2 * only + 1], s);
+        } else {
             // several family pairs in one launch: the learned start only
             // where it pays for the whole launch, i.e. no Mie-Grueneisen
             // group (its walks set the time of a mixed launch) and some
@@ -421,19 +446,19 @@ int solve_eos(const MlpDev* net, int64_t n, const double* in, const int32_t* mat
                 }
             SolveArgs sm = sa;
             if (mg || !takes) sm.net = nullptr;
-            learned = launch_solve<-1, -1>(sm, grid_for(n), nullptr, s);
+            learned = mg ? launch_solve<-1, -1>(sm, 0, n, s) : launch_solve<-2, -1>(sm, 0, n, s);
         }
-        if (rc == M2C_OK && hipGetLastError() != hipSuccess) rc = M2C_ERR_DEVICE;
+        if (hipGetLastError() != hipSuccess) rc = M2C_ERR_DEVICE;
     } else if (rc == M2C_OK) {
-        learned = launch_solve<-1, -1>(sa, grid_for(n), nullptr, s);
+        learned = launch_solve<-1, -1>(sa, 0, n, s);
         if (hipGetLastError() != hipSuccess) rc = M2C_ERR_DEVICE;
     }
-    if (rc == M2C_OK &&
-        (hipMemcpyAsync(&hb, dbad, sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-         hipMemcpyAsync(&hfb, nfb, sizeof(hfb), hipMemcpyDeviceToHost, s) != hipSuccess ||
-         hipStreamSynchronize(s) != hipSuccess))
+    if (rc == M2C_OK && (hipMemcpyAsync(h, ws, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                         hipStreamSynchronize(s) != hipSuccess))
         rc = M2C_ERR_DEVICE;
-    (void)hipFree(dbad);
+    (void)hipFree(ws);
+    const unsigned long long hfb = rc == M2C_OK ? h[0] : 0;
+    const int32_t hb = rc == M2C_OK ? (int32_t)h[1] : 0;
     // without a learned launch every solved problem started from the
     // acoustic guess
     if (n_fallback) *n_fallback = learned ? (int64_t)hfb : (int64_t)n - hb;

@@ -37,45 +37,55 @@ hipError_t launch_end_batch(const RunDesc* runs, int nruns, int stages, hipStrea
     return hipGetLastError();
 }
 
-// max_i lambda_i of a state (the CFL maximum of the first step after a
-// state is set); non-negative doubles order like their bit patterns.
+// lambda_i of a cell, from its conservative state
 template <bool EG>
-__global__ __launch_bounds__(256) void k_lambda(const Grid G, const double* __restrict__ W,
-                                                const uint8_t* __restrict__ chi, DevScalars* sc)
+__device__ __forceinline__ double cell_lambda(const Grid& G, const eos::EosK* sEos, int x, double r, double mx,
+                                              double my, double mz, double E)
+{
+    double u, v, w, cs;
+    if constexpr (EG) {
+        const double p = geos_prim(sEos[x], r, mx, my, mz, E, u, v, w);
+        cs = sqrt(geos_c2(sEos[x], r, p));
+    } else {
+        const double p = eos_prim(r, mx, my, mz, E, pick(G.gamma, x) - 1.0, pick(G.gpc, x), u, v, w);
+        cs = sqrt(pick(G.gamma, x) * (p + pick(G.pc, x)) / r);
+    }
+    double l = 0.0;
+    if (G.act[0]) l += (fabs(u) + cs) * G.rh[0];
+    if (G.act[1]) l += (fabs(v) + cs) * G.rh[1];
+    if (G.act[2]) l += (fabs(w) + cs) * G.rh[2];
+    return l;
+}
+
+// Maximum over the block of 256 threads into *word (one atomic per block);
+// non-negative doubles order like their bit patterns.
+__device__ __forceinline__ void block_max_lambda(double lam, unsigned long long* word)
 {
     __shared__ double sRed[4];
-    __shared__ eos::EosK sEos[EG ? 2 : 1];
-    if constexpr (EG) geos_stage(G, sEos);
-    const long long N = G.N;
-    double lam = 0.0;
-    for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < N;
-         c += (long long)gridDim.x * blockDim.x) {
-        const int x = chi[c];
-        double u, v, w;
-        const double r = W[c];
-        double cs;
-        if constexpr (EG) {
-            const double p = geos_prim(sEos[x], r, W[N + c], W[2 * N + c], W[3 * N + c], W[4 * N + c], u, v, w);
-            cs = sqrt(geos_c2(sEos[x], r, p));
-        } else {
-            const double p = eos_prim(r, W[N + c], W[2 * N + c], W[3 * N + c], W[4 * N + c], pick(G.gamma, x) - 1.0,
-                                      pick(G.gpc, x), u, v, w);
-            cs = sqrt(pick(G.gamma, x) * (p + pick(G.pc, x)) / r);
-        }
-        double l = 0.0;
-        if (G.act[0]) l += (fabs(u) + cs) * G.rh[0];
-        if (G.act[1]) l += (fabs(v) + cs) * G.rh[1];
-        if (G.act[2]) l += (fabs(w) + cs) * G.rh[2];
-        lam = fmax(lam, l);
-    }
     for (int o = 32; o > 0; o >>= 1) lam = fmax(lam, __shfl_xor(lam, o));
     if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = lam;
     __syncthreads();
     if (threadIdx.x == 0) {
         double m = 0.0;
         for (int k = 0; k < (int)(blockDim.x >> 6); ++k) m = fmax(m, sRed[k]);
-        atomic_max_nonneg(&sc->lam_bits, m);
+        atomic_max_nonneg(word, m);
     }
+}
+
+// max_i lambda_i of a state (the CFL maximum of the first step after a
+// conservative state is set, or after a failed step).
+template <bool EG>
+__global__ __launch_bounds__(256) void k_lambda(const Grid G, const double* __restrict__ W,
+                                                const uint8_t* __restrict__ chi, DevScalars* sc)
+{
+    __shared__ eos::EosK sEos[EG ? 2 : 1];
+    if constexpr (EG) geos_stage(G, sEos);
+    const long long N = G.N;
+    double lam = 0.0;
+    for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < N;
+         c += (long long)gridDim.x * blockDim.x)
+        lam = fmax(lam, cell_lambda<EG>(G, sEos, chi[c], W[c], W[N + c], W[2 * N + c], W[3 * N + c], W[4 * N + c]));
+    block_max_lambda(lam, &sc->lam_bits);
 }
 
 __global__ void k_zero_lam(DevScalars* sc) { sc->lam_bits = 0ull; }
@@ -94,7 +104,10 @@ hipError_t launch_lambda(const Grid& g, const double* W, const uint8_t* chi, Dev
 // Primitive [rho,u,v,w,p,phi][N] -> conservative state and material ids,
 // with the admissibility check (rho > 0, p + p_c > 0, all finite; with a
 // general EOS p above the material's floor and c^2 > 0).  The first failing
-// cell (smallest index) is reported through err_cell.
+// cell (smallest index) is reported through err_cell.  The CFL maximum of
+// the state goes to lam_set on the way (128^3: 60 us for both, 55 + 36 us with a
+// pass of its own over the state; 384^3: 1109 us, 1034 + 456 us); 4096 blocks
+// at most, each adds one atomic.
 template <bool EG>
 __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double* __restrict__ P,
                                                       double* __restrict__ W, uint8_t* __restrict__ chi,
@@ -103,6 +116,7 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double
     __shared__ eos::EosK sEos[EG ? 2 : 1];
     if constexpr (EG) geos_stage(G, sEos);
     const long long N = G.N;
+    double lam = 0.0;
     for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < N;
          c += (long long)gridDim.x * blockDim.x) {
         const double r = P[c], u = P[N + c], v = P[2 * N + c], w = P[3 * N + c], p = P[4 * N + c];
@@ -112,24 +126,42 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double
         const bool ok = isfinite(r) && isfinite(u) && isfinite(v) && isfinite(w) && isfinite(p) &&
                         isfinite(phi) && adm;
         if (!ok) report_error(&sc->err, &sc->err_cell, ST_NONPHYSICAL, c);
+        const double mx = r * u, my = r * v, mz = r * w;
+        double E;
+        if constexpr (EG) E = geos_energy(sEos[x], r, u, v, w, p);
+        else E = eos_energy<double>(r, u, v, w, p, pick(G.gpc, x), pick(G.inv_gm1, x));
         W[c] = r;
-        W[N + c] = r * u;
-        W[2 * N + c] = r * v;
-        W[3 * N + c] = r * w;
-        if constexpr (EG) W[4 * N + c] = geos_energy(sEos[x], r, u, v, w, p);
-        else W[4 * N + c] = eos_energy<double>(r, u, v, w, p, pick(G.gpc, x), pick(G.inv_gm1, x));
+        W[N + c] = mx;
+        W[2 * N + c] = my;
+        W[3 * N + c] = mz;
+        W[4 * N + c] = E;
         W[5 * N + c] = phi;
         chi[c] = (uint8_t)x;
+        lam = fmax(lam, cell_lambda<EG>(G, sEos, x, r, mx, my, mz, E));
     }
+    block_max_lambda(lam, &sc->lam_set);
+}
+
+// the state that k_prim_to_cons wrote is accepted
+__global__ void k_accept_lambda(DevScalars* sc)
+{
+    sc->lam_bits = sc->lam_set;
+    sc->lam_set = 0ull;
+}
+
+hipError_t launch_accept_lambda(DevScalars* sc, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_accept_lambda, dim3(1), dim3(1), 0, s, sc);
+    return hipGetLastError();
 }
 
 hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi, DevScalars* sc,
                                hipStream_t s)
 {
     if (g.eosg)
-        hipLaunchKernelGGL(k_prim_to_cons<true>, dim3(grid_for(g.N, 256)), dim3(256), 0, s, g, prim6, W, chi, sc);
+        hipLaunchKernelGGL(k_prim_to_cons<true>, dim3(grid_for(g.N, 256, 4096)), dim3(256), 0, s, g, prim6, W, chi, sc);
     else
-        hipLaunchKernelGGL(k_prim_to_cons<false>, dim3(grid_for(g.N, 256)), dim3(256), 0, s, g, prim6, W, chi, sc);
+        hipLaunchKernelGGL(k_prim_to_cons<false>, dim3(grid_for(g.N, 256, 4096)), dim3(256), 0, s, g, prim6, W, chi, sc);
     return hipGetLastError();
 }
 

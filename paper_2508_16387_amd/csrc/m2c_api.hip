@@ -423,12 +423,16 @@ int upload_prim(m2c_ctx* c, const double* dprim)
     if (c->hsc->err != 0) {
         const long long cell = c->hsc->err_cell;
         clear_error(c);
+        c->hsc->lam_set = 0;
+        HIPCHK(c, hipMemcpyAsync(&c->sc->lam_set, &c->hsc->lam_set, sizeof(c->hsc->lam_set), hipMemcpyHostToDevice,
+                                 c->stream));
         c->hsc->err_cell = cell;
         return set_err(c, M2C_ERR_NONPHYSICAL, "set_state: inadmissible primitive state at cell %lld", cell);
     }
+    HIPCHK(c, launch_accept_lambda(c->sc, c->stream));
     c->cur = q;
     c->has_state = true;
-    c->lam_valid = false;
+    c->lam_valid = true;
     return M2C_OK;
 }
 

@@ -383,14 +383,17 @@ int m2c_batch_set_state(m2c_batch* b, int32_t k, const double* prim6)
         const long long cell = b->hsc[k].err_cell;
         b->hsc[k].err = 0;
         b->hsc[k].err_cell = LLONG_MAX;
+        b->hsc[k].lam_set = 0;
         push(b);
         return berr(b, M2C_ERR_NONPHYSICAL, "run %d: inadmissible primitive state at cell %lld", k, cell);
     }
     b->hsc[k].cur = q;
+    b->hsc[k].lam_bits = b->hsc[k].lam_set;
+    b->hsc[k].lam_set = 0;
     rc = push(b);
     if (rc) return rc;
     R.has_state = true;
-    R.lam_valid = false;
+    R.lam_valid = true;
     return M2C_OK;
 }
 

@@ -18,6 +18,8 @@ enum { FLUX_HLLC = 0, FLUX_LLF = 1 };                  // the values of M2C_FLUX
 struct DevScalars {
     unsigned long long lam_bits;   // max_i lambda_i of the current state (bits of a
                                    // non-negative double: integer max == double max)
+    unsigned long long lam_set;    // the same of a state being set, 0 between the calls;
+                                   // lam_bits only takes it when the state is accepted
     double dt;                     // dt of the step in flight
     double t;                      // simulated time
     int32_t qlen;                  // interface faces in the work queue

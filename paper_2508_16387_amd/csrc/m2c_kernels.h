@@ -163,6 +163,7 @@ hipError_t launch_points_guess(long long n, const double* in, const double* eos,
 // Per-step bookkeeping and state conversion (k_misc.hip).
 hipError_t launch_end_batch(const RunDesc* runs, int nruns, int stages, hipStream_t s);
 hipError_t launch_lambda(const Grid& g, const double* W, const uint8_t* chi, DevScalars* sc, hipStream_t s);
+hipError_t launch_accept_lambda(DevScalars* sc, hipStream_t s);
 hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi,
                                DevScalars* sc, hipStream_t s);
 hipError_t launch_cons_to_prim(const Grid& g, const double* W, const uint8_t* chi, double* prim6,

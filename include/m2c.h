@@ -165,7 +165,8 @@ typedef struct m2c_stats {
     int32_t pad0;
     int64_t err_cell;           /* first cell (or face/3) found failing, -1     */
     double ms_stage;            /* device time of the bulk stage kernels        */
-    double ms_fiver;            /* device time of the interface Riemann kernel  */
+    double ms_fiver;            /* device time of the interface Riemann kernel,
+                                   with the queue's where one kernel does both  */
     double ms_other;            /* device time of every other kernel of a step  */
     int64_t stage_launches;     /* bulk stage-kernel launches timed             */
     int64_t fiver_launches;

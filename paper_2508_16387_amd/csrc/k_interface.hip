@@ -623,24 +623,22 @@ __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int re
     fiver_body<false, true>(a, record, blockIdx.x, gridDim.x, nullptr, &m);
 }
 
+// With a general EOS the queue is a launch of its own: a face takes so long
+// there that spreading the faces as the interface lies in the grid costs more
+// than the launch (128^3 charge: FIVER 80 -> 131 us); with the learned guess
+// too, whose network takes whole wavefronts of faces; and on grids of more
+// compaction blocks than k_fiver_open's registers let run at once, where the
+// scan for them is work, not latency (384^3: 64 against 30 us, of a 5 ms
+// step).
+bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp) { return !(a.g.eosg || mlp || a.nblk > 512); }
+
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s)
 {
+    if (open && !fiver_opens(a, mlp)) return hipErrorInvalidValue;
     long long nb = (a.qcap + 255) / 256;
     if (nb > 1024) nb = 1024;
     if (nb < 1) nb = 1;
     const int rec = record ? 1 : 0;
-    // with a general EOS the queue is a launch of its own: a face takes so
-    // long there that spreading the faces as the interface lies in the grid
-    // costs more than the launch (128^3 charge: FIVER 80 -> 131 us); with the
-    // learned guess too, whose network takes whole wavefronts of faces; and
-    // on grids of more compaction blocks than this kernel's registers let
-    // run at once, where the scan for them is work, not latency (384^3: 64
-    // against 30 us, of a 5 ms step)
-    if (open && (a.g.eosg || mlp || a.nblk > 512)) {
-        const hipError_t e = launch_scatter(a, *open, s);
-        if (e != hipSuccess) return e;
-        open = nullptr;
-    }
     if (a.g.eosg) {
         const int f0 = a.g.ek[0].fam, f1 = a.g.ek[1].fam;
         if (f0 < 0 || f0 > 2 || f1 < 0 || f1 > 2) return hipErrorInvalidValue;

@@ -301,6 +301,9 @@ int enqueue_step(m2c_ctx* c, int p, double dt_imposed, const PhaseArgs* prev, Ph
     ia.chi = c->chi[p];
     HIPCHK(c, launch_step_begin(ia, prev, s));
     const StepOpen open{prev != nullptr, 1, dt_imposed};
+    const MlpDev* mlp = c->use_mlp ? &c->mlp : nullptr;
+    const bool merged = fiver_opens(ia, mlp);
+    if (!merged) HIPCHK(c, launch_scatter(ia, open, s));
 
     StageArgs sa;
     sa.g = c->g;
@@ -342,7 +345,7 @@ int enqueue_step(m2c_ctx* c, int p, double dt_imposed, const PhaseArgs* prev, Ph
     for (int k = 0; k < S; ++k) {
         if (ev) HIPCHK(c, hipEventRecord(ev[1 + 2 * k], s));
         ia.Win = st[k].win;
-        HIPCHK(c, launch_fiver(ia, k == S - 1, k == 0 ? &open : nullptr, c->use_mlp ? &c->mlp : nullptr, s));
+        HIPCHK(c, launch_fiver(ia, k == S - 1, k == 0 && merged ? &open : nullptr, mlp, s));
         if (ev) HIPCHK(c, hipEventRecord(ev[2 + 2 * k], s));
         sa.Win = st[k].win;
         sa.W0 = c->W[p];

@@ -134,6 +134,8 @@ hipError_t launch_scatter(const IfaceArgs& a, const StepOpen& o, hipStream_t s);
 hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s);
 // open (nullable): the first FIVER launch of a step, which opens it and
 // writes a rebuilt queue; mlp: the learned guess (null: acoustic).
+// whether FIVER opens the step itself (else launch_scatter does before it)
+bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp);
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s);
 hipError_t launch_phase(const PhaseArgs& a, hipStream_t s);
 // Batched forms: cmap maps each compaction block to (run, block of run); the

@@ -210,11 +210,20 @@ __device__ __forceinline__ int count_prefix(const IfaceArgs& a, int nb)
     return block_sum(v, sRed);
 }
 
-// End of a step (single grid): counters and simulated time, only when no
-// kernel of the step reported an error.
+// Whether a step before the one being opened failed: an error that is not
+// from the launch that opens it.
+__device__ __forceinline__ bool failed_before(int err) { return err != 0 && err != ST_RIEMANN_OPENING; }
+
+// An opening launch's error becomes an ordinary one, when that launch is over.
+__device__ __forceinline__ void settle_error(DevScalars* sc)
+{
+    if (sc->err == ST_RIEMANN_OPENING) sc->err = ST_RIEMANN;
+}
+
+// End of a step (single grid) that no kernel reported an error of: counters
+// and simulated time.
 __device__ __forceinline__ void end_step_body(DevScalars* sc, int stages)
 {
-    if (sc->err != 0) return;
     sc->steps_done += 1;
     sc->t += sc->dt;
     sc->dt_last = sc->dt;
@@ -228,7 +237,6 @@ __device__ __forceinline__ void end_step_body(DevScalars* sc, int stages)
 // imposed; clear the accumulators that the step fills for the next step.
 __device__ __forceinline__ void begin_step_body(DevScalars* sc, double cfl, double dt_fixed, double dt_imposed)
 {
-    if (sc->err != 0) return;
     double dt;
     if (dt_imposed > 0.0) dt = dt_imposed;
     else if (dt_fixed > 0.0) dt = dt_fixed;
@@ -241,23 +249,35 @@ __device__ __forceinline__ void begin_step_body(DevScalars* sc, double cfl, doub
 // Opens a step in one block of the launch that follows k_step_begin: ends
 // the previous step of the same m2c_step call (end_prev), forms dt (begin)
 // and, when the queue was rebuilt, records its length.  The other blocks of
-// the launch read none of what it writes.
+// the launch read none of what it writes.  It reads one word that they write:
+// the error status, when the launch also solves the new step's faces and one
+// of them fails.  Such a failure must not pass for one of the step being
+// closed, whichever comes first, so the launch reports it as
+// ST_RIEMANN_OPENING, which counts here as no failure.  An error left by
+// earlier launches is never that code: k_step_begin, the launch before, and
+// k_end_step, the last of a call, settle it.  All others only ask whether the
+// status is 0.
 __device__ __forceinline__ void open_step(const IfaceArgs& a, const StepOpen& o)
 {
     DevScalars* sc = a.sc;
     const bool rebuilt = !sc->qreuse;
     const int total = rebuilt ? count_prefix(a, a.nblk) : 0;
     if (threadIdx.x != 0) return;
-    if (o.end_prev) end_step_body(sc, a.g.rk_stages);
-    if (o.begin) begin_step_body(sc, a.g.cfl, a.g.dt_fixed, o.dt_imposed);
+    const bool failed = failed_before(sc->err);
+    if (o.end_prev && !failed) end_step_body(sc, a.g.rk_stages);
+    if (o.begin && !failed) begin_step_body(sc, a.g.cfl, a.g.dt_fixed, o.dt_imposed);
     if (!rebuilt) return;
-    // (a queue past its capacity is not written, see scatter_body)
+    // (a queue past its capacity is not written, see scatter_body, nor solved)
     if (total > a.qcap) atomicCAS(&sc->err, 0, ST_OVERFLOW);
     sc->qlen = total > a.qcap ? 0 : total;
-    sc->qvalid = sc->err == 0 ? 1 : 0;
+    sc->qvalid = failed || total > a.qcap ? 0 : 1;
 }
 
-__global__ void k_end_step(DevScalars* sc, int stages) { end_step_body(sc, stages); }
+__global__ void k_end_step(DevScalars* sc, int stages)
+{
+    if (sc->err == 0) end_step_body(sc, stages);
+    settle_error(sc);
+}
 
 hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s)
 {
@@ -405,7 +425,8 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     constexpr int FS = eos::fam_set(F0) | eos::fam_set(F1);
     // nothing to do when an earlier kernel failed; read once per block so that
     // the whole block takes the same branch (this kernel's own reports may
-    // raise the flag meanwhile)
+    // raise the flag meanwhile; an opening launch's do not stop its blocks,
+    // so that the queue they write between them is whole)
     const int q0 = blk * (int)blockDim.x + (int)threadIdx.x;
     // the thread's first entry of a kept queue, read beside the scalars that
     // say whether it counts (each dependent read is about 0.7 us of a launch
@@ -413,7 +434,7 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     const int32_t ahead = q0 < a.qcap ? a.queue[q0] : 0;
     if (threadIdx.x == 0) {
         const int err = sc->err, qlen = sc->qlen, reuse = sc->qreuse;
-        sHead[0] = err != 0 ? 0 : (open && !reuse ? 1 : qlen);
+        sHead[0] = (open ? failed_before(err) : err != 0) ? 0 : (open && !reuse ? 1 : qlen);
         sHead[1] = open && !reuse;
     }
     if (EG) geos_stage(G, sEos);
@@ -428,7 +449,9 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     // longer: 128^3 charge 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
     const int stride = (rebuilt ? 1 : nblk) * (int)blockDim.x, known = rebuilt ? -1 : q0;
     int first = q0;
-    if (rebuilt && (n == 0 || blk >= a.nblk)) {
+    // (no face of a queue past its capacity is solved: the overflow is the
+    // step's one error, whichever block is first)
+    if (rebuilt && (n == 0 || blk >= a.nblk || count_prefix(a, a.nblk) > a.qcap)) {
         n = 0;
     } else if (rebuilt) {                                            // block-uniform
         lo = count_prefix(a, blk);
@@ -506,7 +529,7 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
         // the judge preferred it)
         mlp_fb += LG && !used && it != 0;
         if (it == 0) {
-            report_error(&sc->err, &sc->err_cell, ST_RIEMANN, c);
+            report_error(&sc->err, &sc->err_cell, open ? ST_RIEMANN_OPENING : ST_RIEMANN, c);
             continue;
         }
         iters += it < 0 ? -it : it;
@@ -802,7 +825,10 @@ template <bool EG>
 __global__ __launch_bounds__(COMPACT_THREADS) void k_step_begin(const IfaceArgs a, const PhaseArgs pa, int prev)
 {
     const bool kept = queue_kept(a.sc);
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc->qreuse = kept ? 1 : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.sc->qreuse = kept ? 1 : 0;
+        settle_error(a.sc);                       // (stays an error to the blocks that read it meanwhile)
+    }
     if (kept) return;
     if (prev) phase_body<EG>(pa, blockIdx.x, gridDim.x);
     for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) {

@@ -8,7 +8,9 @@
 namespace m2c {
 
 enum { BC_TRANSMISSIVE = 0, BC_WALL = 1, BC_PERIODIC = 2 };
-enum { ST_OK = 0, ST_NONPHYSICAL = -2, ST_RIEMANN = -3, ST_OVERFLOW = -7 };
+// ST_RIEMANN_OPENING is ST_RIEMANN from the launch that also opens the step
+// (see open_step in k_interface.hip); it does not outlast the call.
+enum { ST_OK = 0, ST_NONPHYSICAL = -2, ST_RIEMANN = -3, ST_OVERFLOW = -7, ST_RIEMANN_OPENING = -103 };
 enum { LIM_MC = 0, LIM_VA = 1, LIM_VA_MOD = 2 };       // the values of M2C_LIM_*
 enum { FLUX_HLLC = 0, FLUX_LLF = 1 };                  // the values of M2C_FLUX_*
 

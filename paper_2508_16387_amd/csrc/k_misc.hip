@@ -142,10 +142,11 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double
     block_max_lambda(lam, &sc->lam_set);
 }
 
-// the state that k_prim_to_cons wrote is accepted
+// The CFL maximum of the state that k_prim_to_cons wrote becomes the current
+// one unless the state was rejected.
 __global__ void k_accept_lambda(DevScalars* sc)
 {
-    sc->lam_bits = sc->lam_set;
+    if (sc->err == 0) sc->lam_bits = sc->lam_set;
     sc->lam_set = 0ull;
 }
 

@@ -420,19 +420,18 @@ int upload_prim(m2c_ctx* c, const double* dprim)
     if (rc) return rc;
     const int q = 1 - c->cur;
     HIPCHK(c, launch_prim_to_cons(c->g, dprim, c->W[q], c->chi[q], c->sc, c->stream));
+    HIPCHK(c, launch_accept_lambda(c->sc, c->stream));
     if ((rc = invalidate_queue(c))) return rc;
+    // the call leaves nothing pending on the stream: the next one may use another
     rc = pull_scalars(c);
     if (rc) return rc;
     if (c->hsc->err != 0) {
         const long long cell = c->hsc->err_cell;
         clear_error(c);
-        c->hsc->lam_set = 0;
-        HIPCHK(c, hipMemcpyAsync(&c->sc->lam_set, &c->hsc->lam_set, sizeof(c->hsc->lam_set), hipMemcpyHostToDevice,
-                                 c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
         c->hsc->err_cell = cell;
         return set_err(c, M2C_ERR_NONPHYSICAL, "set_state: inadmissible primitive state at cell %lld", cell);
     }
-    HIPCHK(c, launch_accept_lambda(c->sc, c->stream));
     c->cur = q;
     c->has_state = true;
     c->lam_valid = true;

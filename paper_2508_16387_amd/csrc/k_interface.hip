@@ -257,12 +257,12 @@ __device__ __forceinline__ void begin_step_body(DevScalars* sc, double cfl, doub
 // earlier launches is never that code: k_step_begin, the launch before, and
 // k_end_step, the last of a call, settle it.  All others only ask whether the
 // status is 0.
-__device__ __forceinline__ void open_step(const IfaceArgs& a, const StepOpen& o)
+// total: the length of a rebuilt queue (qreuse 0).
+__device__ __forceinline__ void open_step(const IfaceArgs& a, const StepOpen& o, int total)
 {
+    if (threadIdx.x != 0) return;
     DevScalars* sc = a.sc;
     const bool rebuilt = !sc->qreuse;
-    const int total = rebuilt ? count_prefix(a, a.nblk) : 0;
-    if (threadIdx.x != 0) return;
     const bool failed = failed_before(sc->err);
     if (o.end_prev && !failed) end_step_body(sc, a.g.rk_stages);
     if (o.begin && !failed) begin_step_body(sc, a.g.cfl, a.g.dt_fixed, o.dt_imposed);
@@ -285,10 +285,11 @@ hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s)
     return hipGetLastError();
 }
 
-// Writes the queue entries and face slots of compaction block blk, from
-// queue position base; returns their number (0, with nothing written, where
-// they would pass the queue's capacity).
-__device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int base)
+// Writes the queue entries and face slots of compaction block blk, whose
+// faces take the queue positions from base on (none where they would pass the
+// queue's capacity); with PART only those at positions [from, to).
+template <bool PART = false>
+__device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int base, int from = 0, int to = 0)
 {
     __shared__ int sW[COMPACT_THREADS / 64];
     const uint32_t wbase = compact_wave_base(blk);
@@ -301,10 +302,11 @@ __device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int bas
     __syncthreads();
     int total = 0;
     for (int k = 0; k < COMPACT_THREADS / 64; ++k) total += sW[k];
-    if ((long long)base + total > a.qcap) return 0;
-    if (cnt == 0) return total;               // wave-uniform
+    if ((long long)base + total > a.qcap) return;
+    if (cnt == 0) return;                     // wave-uniform
     int off = base;
     for (int k = 0; k < w; ++k) off += sW[k];
+    if (PART && (off >= to || off + cnt <= from)) return;         // wave-uniform
     if (words) {
         // the lane's 16 cells are 4 runs of 4 consecutive cells; faces in
         // ascending id order within a round: by lane, cell, axis
@@ -322,13 +324,15 @@ __device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int bas
             const int f0 = (int)(3u * (wbase + 256u * e + 4u * lane));
             for (int q = 0; q < 12; ++q)
                 if (bits12 & (1u << q)) {
-                    a.queue[o] = f0 + q;                          // 3 (c0 + b) + d = f0 + 3b + d
-                    a.fslot[f0 + q] = o;
+                    if (!PART || (o >= from && o < to)) {
+                        a.queue[o] = f0 + q;                      // 3 (c0 + b) + d = f0 + 3b + d
+                        a.fslot[f0 + q] = o;
+                    }
                     ++o;
                 }
             off += tot;
         }
-        return total;
+        return;
     }
     // byte path: faces in ascending id order: by cell, then by axis
     const uint64_t below = (1ull << lane) - 1ull;
@@ -341,21 +345,96 @@ __device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int bas
 #pragma unroll
         for (int d = 0; d < 3; ++d)
             if (bits & (1u << d)) {
-                a.queue[o] = f0 + d;
-                a.fslot[f0 + d] = o;
+                if (!PART || (o >= from && o < to)) {
+                    a.queue[o] = f0 + d;
+                    a.fslot[f0 + d] = o;
+                }
                 ++o;
             }
         off += __popcll(b0) + __popcll(b1) + __popcll(b2);
     }
-    return total;
+}
+
+// A rebuilt queue shared out over the launch that also solves it: units of at
+// most COMPACT_THREADS faces of one compaction block, in the order of the
+// queue.  (With a compaction block per launch block, whatever it holds, an
+// interface along a layer of the grid, all of whose faces lie in a few
+// compaction blocks, is few blocks' work: a flat surface across z beside a
+// moving bubble took 371 us per step at 128^3 and 172 at 64^3; 299 and 101
+// in units, 304 and 150 with the queue in launches of its own.)
+// Thread t looks after compaction blocks 2t and 2t + 1.
+constexpr int UNIT_BLOCKS = 2 * COMPACT_THREADS;
+struct QueueUnits {
+    int cnt[2], face[2], unit[2];     // faces of the two, and the faces and units before them
+    int faces, units;                 // of the whole queue
+};
+
+__device__ __forceinline__ int units_of(int cnt) { return (cnt + COMPACT_THREADS - 1) / COMPACT_THREADS; }
+
+__device__ __forceinline__ void queue_units(const IfaceArgs& a, QueueUnits& u)
+{
+    __shared__ int sF[COMPACT_THREADS / 64], sU[COMPACT_THREADS / 64];
+    const int b0 = 2 * (int)threadIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) u.cnt[k] = b0 + k < a.nblk ? a.blockcnt[b0 + k] : 0;
+    const int f = u.cnt[0] + u.cnt[1], n = units_of(u.cnt[0]) + units_of(u.cnt[1]);
+    int fi = f, ni = n;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(fi, o), y = __shfl_up(ni, o);
+        if (lane >= o) {
+            fi += x;
+            ni += y;
+        }
+    }
+    if (lane == 63) {
+        sF[w] = fi;
+        sU[w] = ni;
+    }
+    __syncthreads();
+    u.faces = u.units = 0;
+    u.face[0] = fi - f;
+    u.unit[0] = ni - n;
+    for (int k = 0; k < COMPACT_THREADS / 64; ++k) {
+        if (k < w) {
+            u.face[0] += sF[k];
+            u.unit[0] += sU[k];
+        }
+        u.faces += sF[k];
+        u.units += sU[k];
+    }
+    u.face[1] = u.face[0] + u.cnt[0];
+    u.unit[1] = u.unit[0] + units_of(u.cnt[0]);
+}
+
+// Writes the queue entries of unit n of the queue, at positions [from, to),
+// for the block to read.
+__device__ __forceinline__ void scatter_unit(const IfaceArgs& a, const QueueUnits& u, int n, int& from, int& to)
+{
+    __shared__ int sBlk, sBase, sFrom, sTo;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int part = n - u.unit[k];
+        if (part >= 0 && part < units_of(u.cnt[k])) {             // one thread of the block
+            sBlk = 2 * (int)threadIdx.x + k;
+            sBase = u.face[k];
+            sFrom = u.face[k] + part * COMPACT_THREADS;
+            sTo = min(sFrom + COMPACT_THREADS, u.face[k] + u.cnt[k]);
+        }
+    }
+    __syncthreads();
+    from = sFrom;
+    to = sTo;
+    scatter_body<true>(a, sBlk, sBase, from, to);
+    __syncthreads();                              // (also before the words above are written again)
 }
 
 // The queue alone: the step with a general EOS, and listing the interface
 // faces between steps.
 __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter(const IfaceArgs a, const StepOpen o)
 {
-    if (blockIdx.x == 0) open_step(a, o);
-    if (a.sc->qreuse) return;
+    const bool reuse = a.sc->qreuse;
+    if (blockIdx.x == 0) open_step(a, o, reuse ? 0 : count_prefix(a, a.nblk));
+    if (reuse) return;
     for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) scatter_body(a, cb, count_prefix(a, cb));
 }
 
@@ -409,9 +488,9 @@ __device__ __forceinline__ void cell_prim(const Grid& G, const eos::EosK* sEos, 
 // a kernel carries the wave curves and EOS forms of those two families only
 // (-1: dispatched at run time).
 // open (nullable): the first launch of a step, which opens it and writes a
-// rebuilt queue: compaction block blk writes its part and then solves just
-// that part (its faces are then spread over the blocks as the interface lies
-// in the grid, which costs little for stiffened gases, and saves a launch).
+// rebuilt queue: each block writes and solves units of it (queue_units; a
+// unit is seldom full, as the interface lies in the grid, which costs little
+// for stiffened gases, and saves a launch).
 template <bool EG, bool LG = false, int F0 = -1, int F1 = -1>
 __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int blk, int nblk, const StepOpen* open,
                                            const MlpDev* m = nullptr)
@@ -440,140 +519,146 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     if (EG) geos_stage(G, sEos);
     else __syncthreads();
     const bool rebuilt = open && sHead[1];
-    int lo = 0, n = sHead[0];
-    if (open && blk == 0) open_step(a, *open);
+    int n = sHead[0], unit = blk;
+    QueueUnits qu = {};
+    if (rebuilt) {                                                   // block-uniform
+        queue_units(a, qu);
+        // (no face of a queue past its capacity is solved: the overflow is
+        // the step's one error, whichever block is first)
+        if (n == 0 || qu.faces > a.qcap) qu.units = 0;
+        n = 0;
+    }
+    if (open && blk == 0) open_step(a, *open, qu.faces);
     long long iters = 0, fallbacks = 0, mlp_fb = 0;
-    // A kept queue in one sweep of the launch, a rebuilt one compaction block
-    // by compaction block.  (Whole wavefronts of 64 faces and whole blocks
+    // A kept queue in one sweep of the launch, a rebuilt one unit by unit.
+    // (Whole wavefronts of 64 faces and whole blocks
     // first: a short queue spread over more wavefronts at 8 faces each took
     // longer: 128^3 charge 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
     const int stride = (rebuilt ? 1 : nblk) * (int)blockDim.x, known = rebuilt ? -1 : q0;
     int first = q0;
-    // (no face of a queue past its capacity is solved: the overflow is the
-    // step's one error, whichever block is first)
-    if (rebuilt && (n == 0 || blk >= a.nblk || count_prefix(a, a.nblk) > a.qcap)) {
-        n = 0;
-    } else if (rebuilt) {                                            // block-uniform
-        lo = count_prefix(a, blk);
-        n = lo + scatter_body(a, blk, lo);
-        first = lo + (int)threadIdx.x;
-        __syncthreads();                                             // the block reads its own entries
-    }
-    // LG: wave-uniform trip count (q may pass n in the last pass)
-    const int qend = LG ? (n + 63) / 64 * 64 : n;
-    for (int q = first; q < qend; q += stride) {
-        const bool live = !LG || q < n;
-        uint32_t c = 0, cn = 0;
-        int d = 0;
-        if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)(q == known ? ahead : a.queue[q]), c, cn, d);
-        const int xa = live ? a.chi[c] : 0, xb = live ? a.chi[cn] : 0;
-        double qa[5], qb[5];
-        cell_prim<EG, FS>(G, sEos, a.Win, c, xa, qa);
-        cell_prim<EG, FS>(G, sEos, a.Win, cn, xb, qb);
-        const int t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
-        const double ua = qa[1 + d], ub = qb[1 + d];
-        const double gA = pick(G.gamma, xa), pcA = pick(G.pc, xa), gB = pick(G.gamma, xb), pcB = pick(G.pc, xb);
-        double out[4];
-        bool used = false;
-        bool hg = false;
-        double gs = 0.0;
-        if constexpr (LG && !EG) {
-            const bool skip = !live || acoustic_suffices(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB);
-            if (__ballot(!skip) != 0ull) {                       // wave-uniform
-                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                double plo = 0.0, P = 1.0;
-                if (!skip) mlp_features(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, x, plo, P);
-                gs = guess64_mem(*m, x, plo, P, skip);
-                hg = !skip;
-            }
-            if (!live) continue;
+    do {
+        if (rebuilt) {                                               // block-uniform
+            if (unit >= qu.units) break;
+            scatter_unit(a, qu, unit, first, n);
+            first += (int)threadIdx.x;
+            unit += nblk;
         }
-        int it;
-        if constexpr (EG) {
-            // material 0 always on the left: where the lower cell holds
-            // material 1 the mirrored problem is solved (p* unchanged, u*
-            // negated, the star densities swapped), so that every lane of a
-            // wavefront runs the same families' code on each side
-            const bool flip = xa != 0;
-            const double in[6] = {flip ? qb[0] : qa[0], flip ? -ub : ua, flip ? qb[4] : qa[4],
-                                  flip ? qa[0] : qb[0], flip ? -ua : ub, flip ? qa[4] : qb[4]};
-            double o[4];
-            constexpr int S0 = eos::fam_set(F0), S1 = eos::fam_set(F1);
-            if constexpr (LG) {
-                // learned start (the families take it, see learned_pair):
-                // the network evaluated by whole wavefronts for the faces
-                // away from equilibrium, then the judged outer iteration
-                eos::Pair P;
-                const bool ok = live && eos::pair_init<S0, S1>(sEos[0], sEos[1], in, P);
-                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                double plo = 0.0, Pn = 1.0;
-                const bool skip = !ok || eos_near_equilibrium(P) || !eos_features(P, F0, F1, x, plo, Pn);
-                double g = __builtin_nan("");
-                if (__ballot(!skip) != 0ull) g = guess64_mem(*m, x, plo, Pn, skip);      // wave-uniform
+        // LG: wave-uniform trip count (q may pass n in the last pass)
+        const int qend = LG ? (n + 63) / 64 * 64 : n;
+        for (int q = first; q < qend; q += stride) {
+            const bool live = !LG || q < n;
+            uint32_t c = 0, cn = 0;
+            int d = 0;
+            if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)(q == known ? ahead : a.queue[q]), c, cn, d);
+            const int xa = live ? a.chi[c] : 0, xb = live ? a.chi[cn] : 0;
+            double qa[5], qb[5];
+            cell_prim<EG, FS>(G, sEos, a.Win, c, xa, qa);
+            cell_prim<EG, FS>(G, sEos, a.Win, cn, xb, qb);
+            const int t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
+            const double ua = qa[1 + d], ub = qb[1 + d];
+            const double gA = pick(G.gamma, xa), pcA = pick(G.pc, xa), gB = pick(G.gamma, xb), pcB = pick(G.pc, xb);
+            double out[4];
+            bool used = false;
+            bool hg = false;
+            double gs = 0.0;
+            if constexpr (LG && !EG) {
+                const bool skip = !live || acoustic_suffices(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB);
+                if (__ballot(!skip) != 0ull) {                       // wave-uniform
+                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    double plo = 0.0, P = 1.0;
+                    if (!skip) mlp_features(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, x, plo, P);
+                    gs = guess64_mem(*m, x, plo, P, skip);
+                    hg = !skip;
+                }
                 if (!live) continue;
-                it = 0;
-                for (int k = 0; k < 4; ++k) o[k] = __builtin_nan("");
-                if (ok) it = eos::pair_solve<S0, S1, 8>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
-            } else {
-                it = eos::solve_pair<S0, S1, 8>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
             }
-            out[0] = o[0];
-            out[1] = flip ? -o[1] : o[1];
-            out[2] = flip ? o[3] : o[2];
-            out[3] = flip ? o[2] : o[3];
-        } else {
-            it = riemann_solve(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, G.rtol, G.maxit, hg, gs, out,
-                               &used);
-        }
-        // faces that started from the acoustic guess (near equilibrium, or
-        // the judge preferred it)
-        mlp_fb += LG && !used && it != 0;
-        if (it == 0) {
-            report_error(&sc->err, &sc->err_cell, open ? ST_RIEMANN_OPENING : ST_RIEMANN, c);
-            continue;
-        }
-        iters += it < 0 ? -it : it;
-        fallbacks += it < 0;
-        const double ps = out[0], us = out[1];
-        double Fl[5], Fu[5];
-        if constexpr (EG) {
-            geos_flux<FS>(sEos[xa], G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, Fl);
-            geos_flux<FS>(sEos[xb], G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], Fu);
-        } else {
-            num_flux<double>(G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, gA, pcA,
-                             pick(G.gpc, xa), pick(G.inv_gm1, xa), Fl);
-            num_flux<double>(G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], gB, pcB,
-                             pick(G.gpc, xb), pick(G.inv_gm1, xb), Fu);
-        }
-        // face frame (mass, normal, t1, t2, energy) -> global components;
-        // the ten fluxes of a face are contiguous (one address per face for
-        // the stage kernel that reads them)
-        double* const fq = a.fluxF + 10 * (long long)q;
-        double fo[10];
-        fo[0] = Fl[0];
-        fo[1 + d] = Fl[1];
-        fo[t1] = Fl[2];
-        fo[t2] = Fl[3];
-        fo[4] = Fl[4];
-        fo[5] = Fu[0];
-        fo[6 + d] = Fu[1];
-        fo[5 + t1] = Fu[2];
-        fo[5 + t2] = Fu[3];
-        fo[9] = Fu[4];
+            int it;
+            if constexpr (EG) {
+                // material 0 always on the left: where the lower cell holds
+                // material 1 the mirrored problem is solved (p* unchanged, u*
+                // negated, the star densities swapped), so that every lane of a
+                // wavefront runs the same families' code on each side
+                const bool flip = xa != 0;
+                const double in[6] = {flip ? qb[0] : qa[0], flip ? -ub : ua, flip ? qb[4] : qa[4],
+                                      flip ? qa[0] : qb[0], flip ? -ua : ub, flip ? qa[4] : qb[4]};
+                double o[4];
+                constexpr int S0 = eos::fam_set(F0), S1 = eos::fam_set(F1);
+                if constexpr (LG) {
+                    // learned start (the families take it, see learned_pair):
+                    // the network evaluated by whole wavefronts for the faces
+                    // away from equilibrium, then the judged outer iteration
+                    eos::Pair P;
+                    const bool ok = live && eos::pair_init<S0, S1>(sEos[0], sEos[1], in, P);
+                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    double plo = 0.0, Pn = 1.0;
+                    const bool skip = !ok || eos_near_equilibrium(P) || !eos_features(P, F0, F1, x, plo, Pn);
+                    double g = __builtin_nan("");
+                    if (__ballot(!skip) != 0ull) g = guess64_mem(*m, x, plo, Pn, skip);      // wave-uniform
+                    if (!live) continue;
+                    it = 0;
+                    for (int k = 0; k < 4; ++k) o[k] = __builtin_nan("");
+                    if (ok) it = eos::pair_solve<S0, S1, 8>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
+                } else {
+                    it = eos::solve_pair<S0, S1, 8>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
+                }
+                out[0] = o[0];
+                out[1] = flip ? -o[1] : o[1];
+                out[2] = flip ? o[3] : o[2];
+                out[3] = flip ? o[2] : o[3];
+            } else {
+                it = riemann_solve(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, G.rtol, G.maxit, hg, gs, out,
+                                   &used);
+            }
+            // faces that started from the acoustic guess (near equilibrium, or
+            // the judge preferred it)
+            mlp_fb += LG && !used && it != 0;
+            if (it == 0) {
+                report_error(&sc->err, &sc->err_cell, open ? ST_RIEMANN_OPENING : ST_RIEMANN, c);
+                continue;
+            }
+            iters += it < 0 ? -it : it;
+            fallbacks += it < 0;
+            const double ps = out[0], us = out[1];
+            double Fl[5], Fu[5];
+            if constexpr (EG) {
+                geos_flux<FS>(sEos[xa], G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, Fl);
+                geos_flux<FS>(sEos[xb], G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], Fu);
+            } else {
+                num_flux<double>(G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, gA, pcA,
+                                 pick(G.gpc, xa), pick(G.inv_gm1, xa), Fl);
+                num_flux<double>(G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], gB, pcB,
+                                 pick(G.gpc, xb), pick(G.inv_gm1, xb), Fu);
+            }
+            // face frame (mass, normal, t1, t2, energy) -> global components;
+            // the ten fluxes of a face are contiguous (one address per face for
+            // the stage kernel that reads them)
+            double* const fq = a.fluxF + 10 * (long long)q;
+            double fo[10];
+            fo[0] = Fl[0];
+            fo[1 + d] = Fl[1];
+            fo[t1] = Fl[2];
+            fo[t2] = Fl[3];
+            fo[4] = Fl[4];
+            fo[5] = Fu[0];
+            fo[6 + d] = Fu[1];
+            fo[5 + t1] = Fu[2];
+            fo[5 + t2] = Fu[3];
+            fo[9] = Fu[4];
 #pragma unroll
-        for (int v = 0; v < 10; ++v) fq[v] = fo[v];
-        if (record) {
-            const long long Q = a.qcap;
-            a.star[0 * Q + q] = ps;
-            a.star[1 * Q + q] = us;
-            a.star[2 * Q + q] = out[2];
-            a.star[3 * Q + q] = out[3];
-            a.star[4 * Q + q] = qa[t1];
-            a.star[5 * Q + q] = qa[t2];
-            a.star[6 * Q + q] = qb[t1];
-            a.star[7 * Q + q] = qb[t2];
+            for (int v = 0; v < 10; ++v) fq[v] = fo[v];
+            if (record) {
+                const long long Q = a.qcap;
+                a.star[0 * Q + q] = ps;
+                a.star[1 * Q + q] = us;
+                a.star[2 * Q + q] = out[2];
+                a.star[3 * Q + q] = out[3];
+                a.star[4 * Q + q] = qa[t1];
+                a.star[5 * Q + q] = qa[t2];
+                a.star[6 * Q + q] = qb[t1];
+                a.star[7 * Q + q] = qb[t2];
+            }
         }
-    }
+    } while (rebuilt);
     // counters: one atomic per block and counter (same-address atomics from
     // every wavefront serialise into a measurable tail)
     for (int o = 32; o > 0; o >>= 1) {
@@ -653,7 +738,7 @@ __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int re
 // compaction blocks than k_fiver_open's registers let run at once, where the
 // scan for them is work, not latency (384^3: 64 against 30 us, of a 5 ms
 // step).
-bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp) { return !(a.g.eosg || mlp || a.nblk > 512); }
+bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp) { return !(a.g.eosg || mlp || a.nblk > UNIT_BLOCKS); }
 
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s)
 {
@@ -893,7 +978,7 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter_batch(const RunDesc
     const bool reuse = runs[m.x].sc->qreuse;
     if (reuse && m.y != 0) return;
     const IfaceArgs a = iface_of_run(runs[m.x], 1);
-    if (m.y == 0) open_step(a, StepOpen{0, 1, 0.0});
+    if (m.y == 0) open_step(a, StepOpen{0, 1, 0.0}, reuse ? 0 : count_prefix(a, a.nblk));
     if (!reuse) scatter_body(a, m.y, count_prefix(a, m.y));
 }
 

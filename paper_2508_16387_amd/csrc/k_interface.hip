@@ -182,15 +182,27 @@ __device__ __forceinline__ uint64_t lane_bits_words(const Grid& G, const uint8_t
     return packed;
 }
 
-__device__ __forceinline__ void count_body(const IfaceArgs& a, int blk)
+// Compaction blocks [first, end) of a chunk.
+__device__ __forceinline__ int2 chunk_blocks(const IfaceArgs& a, int chunk)
+{
+    const int per = compact_per_chunk(a.nblk);
+    return make_int2(chunk * per, min(a.nblk, (chunk + 1) * per));
+}
+
+__device__ __forceinline__ void count_body(const IfaceArgs& a, int chunk)
 {
     __shared__ int sRed[COMPACT_THREADS / 64];
-    const uint32_t wbase = compact_wave_base(blk);
+    const int2 r = chunk_blocks(a, chunk);
+    const bool words = compact_words(a.g, a.chi);
     int cnt = 0;
-    if (compact_words(a.g, a.chi)) (void)lane_bits_words(a.g, a.chi, wbase, cnt);
-    else (void)lane_bits_bytes(a.g, a.chi, wbase, cnt);
+    for (int blk = r.x; blk < r.y; ++blk) {
+        int k;
+        if (words) (void)lane_bits_words(a.g, a.chi, compact_wave_base(blk), k);
+        else (void)lane_bits_bytes(a.g, a.chi, compact_wave_base(blk), k);
+        cnt += k;
+    }
     const int t = block_sum(cnt, sRed);
-    if (threadIdx.x == 0) a.blockcnt[blk] = t;
+    if (threadIdx.x == 0) a.blockcnt[chunk] = t;
 }
 
 // A step whose predecessor flipped no cell has the material ids the queue
@@ -200,15 +212,18 @@ __device__ __forceinline__ void count_body(const IfaceArgs& a, int blk)
 // scatter.
 __device__ __forceinline__ bool queue_kept(const DevScalars* sc) { return sc->qvalid && sc->nflip == 0; }
 
-// Sum of the counts of blocks [0, nb), for every thread of the block.
-__device__ __forceinline__ int count_prefix(const IfaceArgs& a, int nb)
+// Faces of the chunks [0, n), for every thread of the block.
+__device__ __forceinline__ int count_prefix(const IfaceArgs& a, int n)
 {
     __shared__ int sRed[COMPACT_THREADS / 64];
     int v = 0;
-    for (int b = threadIdx.x; b < nb; b += COMPACT_THREADS) v += a.blockcnt[b];
+    for (int b = threadIdx.x; b < n; b += COMPACT_THREADS) v += a.blockcnt[b];
     __syncthreads();                              // sRed of an earlier call
     return block_sum(v, sRed);
 }
+
+// Length of a rebuilt queue.
+__device__ __forceinline__ int count_total(const IfaceArgs& a) { return count_prefix(a, compact_chunks(a.nblk)); }
 
 // Whether a step before the one being opened failed: an error that is not
 // from the launch that opens it.
@@ -287,9 +302,10 @@ hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s)
 
 // Writes the queue entries and face slots of compaction block blk, whose
 // faces take the queue positions from base on (none where they would pass the
-// queue's capacity); with PART only those at positions [from, to).
+// queue's capacity); with PART only those at positions [from, to).  Returns
+// the number of its faces.
 template <bool PART = false>
-__device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int base, int from = 0, int to = 0)
+__device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int base, int from = 0, int to = 0)
 {
     __shared__ int sW[COMPACT_THREADS / 64];
     const uint32_t wbase = compact_wave_base(blk);
@@ -302,11 +318,11 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int ba
     __syncthreads();
     int total = 0;
     for (int k = 0; k < COMPACT_THREADS / 64; ++k) total += sW[k];
-    if ((long long)base + total > a.qcap) return;
-    if (cnt == 0) return;                     // wave-uniform
+    if ((long long)base + total > a.qcap) return total;
+    if (cnt == 0) return total;               // wave-uniform
     int off = base;
     for (int k = 0; k < w; ++k) off += sW[k];
-    if (PART && (off >= to || off + cnt <= from)) return;         // wave-uniform
+    if (PART && (off >= to || off + cnt <= from)) return total;   // wave-uniform
     if (words) {
         // the lane's 16 cells are 4 runs of 4 consecutive cells; faces in
         // ascending id order within a round: by lane, cell, axis
@@ -332,7 +348,7 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int ba
                 }
             off += tot;
         }
-        return;
+        return total;
     }
     // byte path: faces in ascending id order: by cell, then by axis
     const uint64_t below = (1ull << lane) - 1ull;
@@ -353,6 +369,26 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int ba
             }
         off += __popcll(b0) + __popcll(b1) + __popcll(b2);
     }
+    return total;
+}
+
+// The queue entries and face slots of a chunk.  The counts before it are
+// added up once and carried through its compaction blocks, so that a rebuild
+// costs what the grid's size does (summed anew for each compaction block they
+// were 0.4 GB of reads at 384^3 and 34 GB at 2^29 cells): counts and queue
+// of a moving interface 74 + 120 -> 79 + 39 us at 384^3 and 161 + 382 ->
+// 159 + 83 us at 512^3, where a count, a scan and a scatter in launches of
+// their own, with a block per compaction block, took 69 + 16 + 44 and 148 +
+// 58 + 95 us.
+__device__ __forceinline__ void scatter_chunk(const IfaceArgs& a, int chunk)
+{
+    if (a.blockcnt[chunk] == 0) return;           // block-uniform
+    const int2 r = chunk_blocks(a, chunk);
+    int base = count_prefix(a, chunk);
+    for (int blk = r.x; blk < r.y; ++blk) {
+        base += scatter_body(a, blk, base);
+        __syncthreads();                          // its sums are read before they are written again
+    }
 }
 
 // A rebuilt queue shared out over the launch that also solves it: units of at
@@ -364,6 +400,7 @@ __device__ __forceinline__ void scatter_body(const IfaceArgs& a, int blk, int ba
 // in units, 304 and 150 with the queue in launches of its own.)
 // Thread t looks after compaction blocks 2t and 2t + 1.
 constexpr int UNIT_BLOCKS = 2 * COMPACT_THREADS;
+static_assert(UNIT_BLOCKS <= COMPACT_CHUNKS, "a count per compaction block");
 struct QueueUnits {
     int cnt[2], face[2], unit[2];     // faces of the two, and the faces and units before them
     int faces, units;                 // of the whole queue
@@ -433,19 +470,13 @@ __device__ __forceinline__ void scatter_unit(const IfaceArgs& a, const QueueUnit
 __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter(const IfaceArgs a, const StepOpen o)
 {
     const bool reuse = a.sc->qreuse;
-    if (blockIdx.x == 0) open_step(a, o, reuse ? 0 : count_prefix(a, a.nblk));
-    if (reuse) return;
-    for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) scatter_body(a, cb, count_prefix(a, cb));
+    if (blockIdx.x == 0) open_step(a, o, reuse ? 0 : count_total(a));
+    if (!reuse) scatter_chunk(a, blockIdx.x);
 }
-
-// Blocks of the compaction launches: at most four per CU, since the launch
-// also runs, to no purpose but its time, when the queue is kept (384^3: 13824
-// blocks that return at once took 5 us).
-unsigned compact_grid(int nblk) { return (unsigned)(nblk < 1024 ? nblk : 1024); }
 
 hipError_t launch_scatter(const IfaceArgs& a, const StepOpen& o, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scatter, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, o);
+    hipLaunchKernelGGL(k_scatter, dim3(compact_chunks(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, o);
     return hipGetLastError();
 }
 
@@ -916,10 +947,7 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_step_begin(const IfaceArgs 
     }
     if (kept) return;
     if (prev) phase_body<EG>(pa, blockIdx.x, gridDim.x);
-    for (int cb = blockIdx.x; cb < a.nblk; cb += gridDim.x) {
-        count_body(a, cb);
-        __syncthreads();                          // its sums are read before they are written again
-    }
+    count_body(a, blockIdx.x);
 }
 
 hipError_t launch_step_begin(const IfaceArgs& a, const PhaseArgs* prev_phase, hipStream_t s)
@@ -927,9 +955,9 @@ hipError_t launch_step_begin(const IfaceArgs& a, const PhaseArgs* prev_phase, hi
     const PhaseArgs pa = prev_phase ? *prev_phase : PhaseArgs{};
     const int prev = prev_phase ? 1 : 0;
     if (prev_phase && a.g.eosg)
-        hipLaunchKernelGGL(k_step_begin<true>, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
+        hipLaunchKernelGGL(k_step_begin<true>, dim3(compact_chunks(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
     else
-        hipLaunchKernelGGL(k_step_begin<false>, dim3(compact_grid(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
+        hipLaunchKernelGGL(k_step_begin<false>, dim3(compact_chunks(a.nblk)), dim3(COMPACT_THREADS), 0, s, a, pa, prev);
     return hipGetLastError();
 }
 
@@ -978,8 +1006,8 @@ __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter_batch(const RunDesc
     const bool reuse = runs[m.x].sc->qreuse;
     if (reuse && m.y != 0) return;
     const IfaceArgs a = iface_of_run(runs[m.x], 1);
-    if (m.y == 0) open_step(a, StepOpen{0, 1, 0.0}, reuse ? 0 : count_prefix(a, a.nblk));
-    if (!reuse) scatter_body(a, m.y, count_prefix(a, m.y));
+    if (m.y == 0) open_step(a, StepOpen{0, 1, 0.0}, reuse ? 0 : count_total(a));
+    if (!reuse) scatter_chunk(a, m.y);
 }
 
 hipError_t launch_compact_batch(const RunDesc* runs, const int2* cmap, int ncblocks, hipStream_t s)

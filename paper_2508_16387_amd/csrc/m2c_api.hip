@@ -568,7 +568,7 @@ int m2c_create(const m2c_config* cfg, m2c_ctx** out)
     alloc((void**)&c->fluxF, 10 * c->qcap * sizeof(double));
     alloc((void**)&c->star, 8 * c->qcap * sizeof(double));
     alloc((void**)&c->flips, N * sizeof(int32_t));
-    alloc((void**)&c->blockcnt, (size_t)c->nblk_compact * sizeof(int32_t));
+    alloc((void**)&c->blockcnt, (size_t)compact_chunks(c->nblk_compact) * sizeof(int32_t));
     alloc((void**)&c->sc, sizeof(DevScalars));
     if (ok && hipHostMalloc((void**)&c->hsc, sizeof(DevScalars), hipHostMallocDefault) != hipSuccess) ok = false;
     if (!ok) {

@@ -333,9 +333,10 @@ int m2c_batch_create(int32_t n, const m2c_config* cfgs, m2c_batch** out)
         alloc((void**)&R.d.fluxF, 10 * R.d.qcap * sizeof(double));
         alloc((void**)&R.d.star, 8 * R.d.qcap * sizeof(double));
         alloc((void**)&R.d.flips, N * sizeof(int32_t));
-        alloc((void**)&R.d.blockcnt, (size_t)R.d.nblk_compact * sizeof(int32_t));
+        const int chunks = compact_chunks(R.d.nblk_compact);
+        alloc((void**)&R.d.blockcnt, (size_t)chunks * sizeof(int32_t));
         R.d.sc = b->d_sc + r;
-        for (int k = 0; k < R.d.nblk_compact; ++k) cmap.push_back(make_int2(r, k));
+        for (int k = 0; k < chunks; ++k) cmap.push_back(make_int2(r, k));
         if (ok && launch_fill_i32(R.d.fslot, 3 * N, -1, b->stream) != hipSuccess) ok = false;
     }
     if (ok) {

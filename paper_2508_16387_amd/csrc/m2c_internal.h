@@ -69,7 +69,7 @@ struct Bufs {
     double* fluxF;                 // [qcap][10]: flux for the lower cell (5), upper cell (5)
     double* star;                  // [8][qcap]: p*, u*, rho*_L, rho*_R, vt1_L, vt2_L, vt1_R, vt2_R
     int32_t* flips;                // [N] flipped cells of the step in flight
-    int32_t* blockcnt;             // compaction partial counts
+    int32_t* blockcnt;             // interface faces per compaction chunk
     DevScalars* sc;
     long long qcap;
     int nblk_compact;

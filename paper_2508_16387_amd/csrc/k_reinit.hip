@@ -151,23 +151,27 @@ __global__ __launch_bounds__(256) void k_reinit_speed(const ReinitGrid g, const 
     constexpr int RZ = BAND ? RZ_BAND : RZ_FULL;
     const uint32_t blk = xcd_run(blockIdx.x, gridDim.x);
     const Tile t = tile_of<BAND>(g, blk);
-    Stencil<RZ> v;
-    load_stencil<RZ>(g, t, phi0, v);
     int any = 0;
+    // (a wavefront past the grid has nothing to do; 1x1x200000, band of two
+    // cells, 11 iterations: 309 us with its loads, 252 without)
+    if (!BAND || __any(t.live)) {                // wave-uniform
+        Stencil<RZ> v;
+        load_stencil<RZ>(g, t, phi0, v);
 #pragma unroll
-    for (int q = 0; q < RZ; ++q) {
-        const double p = v.c[1 + q];
-        const bool pos = p >= 0.0;
-        bool fl = false;
-        if (g.act[0]) fl |= (v.xa[q] >= 0.0) != pos || (v.xb[q] >= 0.0) != pos;
-        if (g.act[1]) fl |= (v.ya[q] >= 0.0) != pos || (v.yb[q] >= 0.0) != pos;
-        if (g.act[2]) fl |= (v.c[q] >= 0.0) != pos || (z_above<RZ>(g, t, v, q) >= 0.0) != pos;
-        double s = p / sqrt(p * p + eps2);
-        if (fl || (BAND && fabs(p) >= band)) s = 0.0;
-        if (t.live && t.k0 + q < g.nz) {
-            S[v.cell[q]] = s;
-            tmp[v.cell[q]] = p;
-            any |= s != 0.0;
+        for (int q = 0; q < RZ; ++q) {
+            const double p = v.c[1 + q];
+            const bool pos = p >= 0.0;
+            bool fl = false;
+            if (g.act[0]) fl |= (v.xa[q] >= 0.0) != pos || (v.xb[q] >= 0.0) != pos;
+            if (g.act[1]) fl |= (v.ya[q] >= 0.0) != pos || (v.yb[q] >= 0.0) != pos;
+            if (g.act[2]) fl |= (v.c[q] >= 0.0) != pos || (z_above<RZ>(g, t, v, q) >= 0.0) != pos;
+            double s = p / sqrt(p * p + eps2);
+            if (fl || (BAND && fabs(p) >= band)) s = 0.0;
+            if (t.live && t.k0 + q < g.nz) {
+                S[v.cell[q]] = s;
+                tmp[v.cell[q]] = p;
+                any |= s != 0.0;
+            }
         }
     }
     if (!BAND) return;
@@ -192,6 +196,7 @@ __global__ __launch_bounds__(256) void k_reinit_step(const ReinitGrid g, const d
     constexpr int RZ = BAND ? RZ_BAND : RZ_FULL;
     const uint32_t b = xcd_run(blockIdx.x, gridDim.x);
     const Tile t = tile_of<BAND>(g, BAND ? (uint32_t)list[1 + b] : b);
+    if (BAND && !__any(t.live)) return;           // wave-uniform
     Stencil<RZ> v;
     double s[RZ];
     load_stencil<RZ>(g, t, phi, v);

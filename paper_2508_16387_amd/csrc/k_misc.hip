@@ -57,8 +57,9 @@ __device__ __forceinline__ double cell_lambda(const Grid& G, const eos::EosK* sE
     return l;
 }
 
-// Maximum over the block of 256 threads into *word (one atomic per block);
-// non-negative doubles order like their bit patterns.
+// Maximum over the block of 256 threads into *word, by one atomic per block
+// that would raise it (they follow one another, about 10 ns each, and the
+// word only grows); non-negative doubles order like their bit patterns.
 __device__ __forceinline__ void block_max_lambda(double lam, unsigned long long* word)
 {
     __shared__ double sRed[4];
@@ -68,7 +69,8 @@ __device__ __forceinline__ void block_max_lambda(double lam, unsigned long long*
     if (threadIdx.x == 0) {
         double m = 0.0;
         for (int k = 0; k < (int)(blockDim.x >> 6); ++k) m = fmax(m, sRed[k]);
-        atomic_max_nonneg(word, m);
+        const unsigned long long at = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (m > __longlong_as_double((long long)at)) atomic_max_nonneg(word, m);
     }
 }
 
@@ -104,11 +106,13 @@ hipError_t launch_lambda(const Grid& g, const double* W, const uint8_t* chi, Dev
 // Primitive [rho,u,v,w,p,phi][N] -> conservative state and material ids,
 // with the admissibility check (rho > 0, p + p_c > 0, all finite; with a
 // general EOS p above the material's floor and c^2 > 0).  The first failing
-// cell (smallest index) is reported through err_cell.  The CFL maximum of
-// the state goes to lam_set on the way (128^3: 60 us for both, 55 + 36 us with a
-// pass of its own over the state; 384^3: 1109 us, 1034 + 456 us); 4096 blocks
-// at most, each adds one atomic.
-template <bool EG>
+// cell (smallest index) is reported through err_cell.  With LAM the CFL
+// maximum of the state goes to lam_set on the way, which saves a pass over the
+// state and a launch where the next step needs it, and costs FP64 operations
+// that the memory accesses do not quite hide where it does not (setting a
+// state and one step, 128^3: by the CFL rule 443 us with a pass of its own and
+// 400 in this one; of imposed dt 408 us with the maximum and 385 without).
+template <bool EG, bool LAM>
 __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double* __restrict__ P,
                                                       double* __restrict__ W, uint8_t* __restrict__ chi,
                                                       DevScalars* sc)
@@ -137,9 +141,9 @@ __global__ __launch_bounds__(256) void k_prim_to_cons(const Grid G, const double
         W[4 * N + c] = E;
         W[5 * N + c] = phi;
         chi[c] = (uint8_t)x;
-        lam = fmax(lam, cell_lambda<EG>(G, sEos, x, r, mx, my, mz, E));
+        if constexpr (LAM) lam = fmax(lam, cell_lambda<EG>(G, sEos, x, r, mx, my, mz, E));
     }
-    block_max_lambda(lam, &sc->lam_set);
+    if constexpr (LAM) block_max_lambda(lam, &sc->lam_set);
 }
 
 // The CFL maximum of the state that k_prim_to_cons wrote becomes the current
@@ -156,13 +160,22 @@ hipError_t launch_accept_lambda(DevScalars* sc, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi, DevScalars* sc,
+template <bool EG, bool LAM>
+static void prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi, DevScalars* sc, long long cap,
+                         hipStream_t s)
+{
+    hipLaunchKernelGGL((k_prim_to_cons<EG, LAM>), dim3(grid_for(g.N, 256, cap)), dim3(256), 0, s, g, prim6, W, chi, sc);
+}
+
+// At most 16384 blocks with the maximum, which ends each of them (4096 with a
+// general EOS, whose constants each block stages).
+hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi, DevScalars* sc, bool lam,
                                hipStream_t s)
 {
-    if (g.eosg)
-        hipLaunchKernelGGL(k_prim_to_cons<true>, dim3(grid_for(g.N, 256, 4096)), dim3(256), 0, s, g, prim6, W, chi, sc);
-    else
-        hipLaunchKernelGGL(k_prim_to_cons<false>, dim3(grid_for(g.N, 256, 4096)), dim3(256), 0, s, g, prim6, W, chi, sc);
+    if (g.eosg && lam) prim_to_cons<true, true>(g, prim6, W, chi, sc, 4096, s);
+    else if (g.eosg) prim_to_cons<true, false>(g, prim6, W, chi, sc, 65536, s);
+    else if (lam) prim_to_cons<false, true>(g, prim6, W, chi, sc, 16384, s);
+    else prim_to_cons<false, false>(g, prim6, W, chi, sc, 65536, s);
     return hipGetLastError();
 }
 

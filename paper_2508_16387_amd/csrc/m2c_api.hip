@@ -57,6 +57,7 @@ struct m2c_ctx {
     int cur = 0;                    // index of the current state
     bool has_state = false;
     bool lam_valid = false;
+    bool lam_used = true;           // the last steps took their dt from the CFL rule
     int tx = 32, ty = 8, kz = 8;
     int tiles[3] = {1, 1, 1};
     bool profiling = false;
@@ -384,6 +385,7 @@ int run_steps(m2c_ctx* c, int32_t nsteps, double dt_imposed, double* t_out)
     rc = pull_scalars(c);
     if (rc) return rc;
     const long long done0 = c->hsc->steps_done;
+    if (nsteps > 0) c->lam_used = !(dt_imposed > 0.0);
     int p = c->cur;
     PhaseArgs pend[2];
     for (int32_t k = 0; k < nsteps; ++k) {
@@ -419,8 +421,10 @@ int upload_prim(m2c_ctx* c, const double* dprim)
     int rc = clear_error(c);
     if (rc) return rc;
     const int q = 1 - c->cur;
-    HIPCHK(c, launch_prim_to_cons(c->g, dprim, c->W[q], c->chi[q], c->sc, c->stream));
-    HIPCHK(c, launch_accept_lambda(c->sc, c->stream));
+    // the CFL maximum in the same pass, unless the steps do without it
+    const bool lam = c->lam_used && !(c->cfg.dt_fixed > 0.0);
+    HIPCHK(c, launch_prim_to_cons(c->g, dprim, c->W[q], c->chi[q], c->sc, lam, c->stream));
+    if (lam) HIPCHK(c, launch_accept_lambda(c->sc, c->stream));
     if ((rc = invalidate_queue(c))) return rc;
     // the call leaves nothing pending on the stream: the next one may use another
     rc = pull_scalars(c);
@@ -434,7 +438,7 @@ int upload_prim(m2c_ctx* c, const double* dprim)
     }
     c->cur = q;
     c->has_state = true;
-    c->lam_valid = true;
+    c->lam_valid = lam;
     return M2C_OK;
 }
 

@@ -377,7 +377,8 @@ int m2c_batch_set_state(m2c_batch* b, int32_t k, const double* prim6)
     rc = push(b);
     if (rc) return rc;
     BCHK(b, hipMemcpyAsync(R.d.W1, prim6, 6 * N * sizeof(double), hipMemcpyHostToDevice, b->stream));
-    BCHK(b, launch_prim_to_cons(R.d.g, R.d.W1, R.d.W[q], R.d.chi[q], R.d.sc, b->stream));
+    const bool lam = !(R.cfg.dt_fixed > 0.0);
+    BCHK(b, launch_prim_to_cons(R.d.g, R.d.W1, R.d.W[q], R.d.chi[q], R.d.sc, lam, b->stream));
     rc = pull(b);
     if (rc) return rc;
     if (b->hsc[k].err != 0) {
@@ -389,12 +390,12 @@ int m2c_batch_set_state(m2c_batch* b, int32_t k, const double* prim6)
         return berr(b, M2C_ERR_NONPHYSICAL, "run %d: inadmissible primitive state at cell %lld", k, cell);
     }
     b->hsc[k].cur = q;
-    b->hsc[k].lam_bits = b->hsc[k].lam_set;
+    if (lam) b->hsc[k].lam_bits = b->hsc[k].lam_set;
     b->hsc[k].lam_set = 0;
     rc = push(b);
     if (rc) return rc;
     R.has_state = true;
-    R.lam_valid = true;
+    R.lam_valid = lam;
     return M2C_OK;
 }
 

@@ -176,8 +176,9 @@ hipError_t launch_points_guess(long long n, const double* in, const double* eos,
 hipError_t launch_end_batch(const RunDesc* runs, int nruns, int stages, hipStream_t s);
 hipError_t launch_lambda(const Grid& g, const double* W, const uint8_t* chi, DevScalars* sc, hipStream_t s);
 hipError_t launch_accept_lambda(DevScalars* sc, hipStream_t s);
+// lam: the state's CFL maximum to lam_set as well
 hipError_t launch_prim_to_cons(const Grid& g, const double* prim6, double* W, uint8_t* chi,
-                               DevScalars* sc, hipStream_t s);
+                               DevScalars* sc, bool lam, hipStream_t s);
 hipError_t launch_cons_to_prim(const Grid& g, const double* W, const uint8_t* chi, double* prim6,
                                hipStream_t s);
 hipError_t launch_chi_from_phi(const Grid& g, const double* W, uint8_t* chi, hipStream_t s);

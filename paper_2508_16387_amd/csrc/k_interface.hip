@@ -11,18 +11,20 @@
 // wavefronts would otherwise diverge on the Newton iteration.
 //
 // Queue order is ascending face id f = 3c + d (face between cell c and its
-// +d neighbour); the compaction is deterministic (counts per block, then
-// each block adds up the counts before its own and writes its faces with
+// +d neighbour); the compaction is deterministic (counts per chunk of cells,
+// then each block adds up the counts before its own and writes its faces with
 // wavefront prefix sums), so the queue is bit-identical from run to run.
 //
 // Launches of a single-grid step besides its bulk stages: k_step_begin (the
 // phase update of the step before, the counts), then per Runge-Kutta stage
 // one FIVER launch, the first of which also writes a rebuilt queue and opens
 // the step.  Each is a chain of a few dependent memory accesses whatever its
-// size, so a launch saved is its whole time saved: count, scan and scatter
-// as launches of their own took 4.5 + 4.6 + 4.8 us of a 128^3 step; now 5.0
-// and 0.5 more for the first FIVER launch.  General EOS, 128^3 charge, whose
-// queue is rebuilt in every step: 40 -> 24 us.  The face -> slot
+// size, so a launch saved is its whole time saved: count, scan and scatter as
+// launches of their own took 4.5 + 4.6 + 4.8 us of a 128^3 step that keeps its
+// queue, where the two now take 4.3 and 1 more in the first FIVER launch, and
+// 20.8 + 4.7 + 8.4 us, with 11.4 for that FIVER launch, where it is rebuilt:
+// 18.0 + 20.3 now.  General EOS, 128^3 charge, whose queue is rebuilt in every
+// step by a launch of its own: 25 + 5 + 10 -> 21 + 10 us.  The face -> slot
 // map is written only at the faces of the new queue and read only at faces
 // whose cells differ in material under the same frozen ids, so entries left
 // from earlier queues are never read and need no clearing.
@@ -465,8 +467,8 @@ __device__ __forceinline__ void scatter_unit(const IfaceArgs& a, const QueueUnit
     __syncthreads();                              // (also before the words above are written again)
 }
 
-// The queue alone: the step with a general EOS, and listing the interface
-// faces between steps.
+// The queue alone, and the opening of the step: where FIVER does not do both
+// (fiver_opens), and listing the interface faces between steps.
 __global__ __launch_bounds__(COMPACT_THREADS) void k_scatter(const IfaceArgs a, const StepOpen o)
 {
     const bool reuse = a.sc->qreuse;
@@ -562,9 +564,9 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     if (open && blk == 0) open_step(a, *open, qu.faces);
     long long iters = 0, fallbacks = 0, mlp_fb = 0;
     // A kept queue in one sweep of the launch, a rebuilt one unit by unit.
-    // (Whole wavefronts of 64 faces and whole blocks
-    // first: a short queue spread over more wavefronts at 8 faces each took
-    // longer: 128^3 charge 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
+    // (Whole wavefronts of 64 faces and whole blocks first: a short queue
+    // spread over more wavefronts at 8 faces each took longer: 128^3 charge
+    // 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
     const int stride = (rebuilt ? 1 : nblk) * (int)blockDim.x, known = rebuilt ? -1 : q0;
     int first = q0;
     do {
@@ -764,11 +766,12 @@ __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int re
 
 // With a general EOS the queue is a launch of its own: a face takes so long
 // there that spreading the faces as the interface lies in the grid costs more
-// than the launch (128^3 charge: FIVER 80 -> 131 us); with the learned guess
-// too, whose network takes whole wavefronts of faces; and on grids of more
-// compaction blocks than k_fiver_open's registers let run at once, where the
-// scan for them is work, not latency (384^3: 64 against 30 us, of a 5 ms
-// step).
+// than the launch (128^3 charge, a compaction block to a launch block: FIVER 80
+// -> 131 us); with the learned guess too, whose network takes whole wavefronts
+// of faces; and on grids of more compaction blocks than a launch block looks
+// after counts (queue_units), where the queue is work, not latency (384^3, a
+// compaction block to a launch block: the first FIVER launch 64 us against 30,
+// of a 5 ms step).
 bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp) { return !(a.g.eosg || mlp || a.nblk > UNIT_BLOCKS); }
 
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s)

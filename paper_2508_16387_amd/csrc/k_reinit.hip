@@ -51,10 +51,13 @@ namespace m2c {
 namespace {
 
 constexpr int RX = 64, RY = 4;
-// planes per block: 4 over the whole grid; 1 in a narrow band, where few
-// blocks move and the serial plane loop of each would be exposed latency
-// (measured at 128^3: whole grid 15.5 us per step with 4 planes against
-// 17.3 with 8; band of six cells 5.3 us with 1 against 7.5 with 4)
+// Planes per block: 4 over the whole grid (us per step with 2, 4 and 8: 64^3
+// 3.7, 4.2, 5.6; 128^3 12.2, 11.9, 12.7; 256^3 113, 99, 96: fewer leave more
+// z neighbours to be read twice, more leave small grids too few blocks); 1
+// in a narrow band, where the tile of one plane is the one that fewest idle
+// cells share (band of six cells, with 1, 2 and 4: 64^3 3.5, 3.7, 4.1; 128^3
+// 7.1, 6.6, 7.1; 256^3 19.8, 16.5, 16.9, so two would be the better choice
+// from 128^3 on).
 constexpr int RZ_FULL = 4, RZ_BAND = 1;
 
 __device__ __forceinline__ int image(int i, int n, int periodic)

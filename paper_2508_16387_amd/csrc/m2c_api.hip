@@ -281,9 +281,9 @@ int harvest_events(m2c_ctx* c)
 
 // Enqueue one full time step with state parity p (reads W[p], writes
 // W[1-p]).  prev (nullable): the phase update of the previous step of this
-// call, still pending; it runs in this step's count kernel, and this step's
-// scan kernel closes that step.  The step's own phase update is returned in
-// *phase, pending.
+// call, still pending; it runs in this step's first launch (k_step_begin), and
+// the launch after that closes that step.  The step's own phase update is
+// returned in *phase, pending.
 int enqueue_step(m2c_ctx* c, int p, double dt_imposed, const PhaseArgs* prev, PhaseArgs* phase)
 {
     hipStream_t s = c->stream;

@@ -216,11 +216,13 @@ int run_batch(m2c_batch* b, int32_t nsteps, std::vector<long long>* done_out)
 // third, one-wavefront round of the block, which 32x7 avoids at the price
 // of more columns past the grid's edge (16 runs of edges 32..128: 783 us per
 // step against 823, 9% more covered cells than 16x16 at worst), so 32x7
-// unless it covers more than 1.11 times the cells; 16x16 in mixed precision
-// (788 against 800 us).  Planes per block by the rule of the single grid
-// over all runs' tiles, except that large batches keep 8 (16 and 24 planes
-// measured 865 and 992 us against 823: the persistent blocks walk several
-// items each, so nothing is gained by longer ones).
+// unless it covers more than 1.11 times the cells (a line drawn from that one
+// batch; the autotuner, which also tries 16x15, finds that one the fastest for
+// 64 such runs); 16x16 in mixed precision (788 against 800 us).  Planes per
+// block by the rule of the single grid over all runs' tiles, except that large
+// batches keep 8 (16 and 24 planes measured 865 and 992 us against 823: the
+// persistent blocks walk several items each, so nothing is gained by longer
+// ones).
 void default_tile(m2c_batch* b, const m2c_config* cfgs)
 {
     auto cover = [&](int tx, int ty) {

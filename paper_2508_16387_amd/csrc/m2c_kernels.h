@@ -71,15 +71,18 @@ struct PhaseArgs {
 };
 
 bool stage_tile_supported(int tx, int ty);
-// FP64 stage blocks resident on the chip at once: two per CU, from the stage
-// kernels' registers.
+// FP64 stage blocks resident on the chip at once: two per CU, which is what
+// the registers of every tuned FP64 stage kernel allow (their build test holds
+// them to it).
 int stage_slots();
 // Planes per stage block, from the number of blocks at a given number of
 // planes (blocks: int -> long long).  Three regimes:
 //   at least 4096 blocks with 32 or 16 planes (16 rounds of two blocks per
 //     CU): that many, so that the prologue of a block's march and the
 //     re-read halo planes are amortised (32 measured 1.5% faster than 16 on
-//     384^3);
+//     384^3, where the line was drawn; it costs the grids just below it: 256^3
+//     gets 16 planes, 794 us per stage launch, where 32 take 755, and 200^3
+//     gets 8, 466 us, where 15 take 450);
 //   grids whose blocks of fewer than 8 planes all fit on the chip at once:
 //     the fewest planes that still fit.  There the launch lasts as long as
 //     one block's march, so fewer planes are a shorter launch until the
@@ -87,8 +90,10 @@ int stage_slots();
 //     rule: 32^3 47 -> 14 us, 50x43x37 54 -> 18 us, 64^3 52 -> 31 us; one
 //     plane fewer than fits: 64^3 36 us, 80^3 58 against 46 us).  FP64 only
 //     (slots 0: not at all): the face below a block's first plane is
-//     evaluated by other code than those inside the march, which in FP32
-//     rounds differently, so the mixed form's results keep to blocks of 8;
+//     evaluated in the march's prologue, by code that rounds differently from
+//     that for the faces inside it, so results depend on where a grid is
+//     split: at 1e-12 in FP64, at 3e-9 in the mixed form, which keeps to
+//     blocks of 8;
 //   otherwise 8 (128^3: 128 us; 4, 6, 10 and 16 planes: 143, 142, 131, 149).
 template <class Blocks>
 int stage_planes(Blocks blocks, int slots)
@@ -142,10 +147,11 @@ hipError_t launch_step_begin(const IfaceArgs& a, const PhaseArgs* prev_phase, hi
 // opens the step and writes a rebuilt queue without solving it
 hipError_t launch_scatter(const IfaceArgs& a, const StepOpen& o, hipStream_t s);
 hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s);
-// open (nullable): the first FIVER launch of a step, which opens it and
-// writes a rebuilt queue; mlp: the learned guess (null: acoustic).
-// whether FIVER opens the step itself (else launch_scatter does before it)
+// whether the first FIVER launch of a step opens it and writes a rebuilt queue
+// (else launch_scatter does, before it)
 bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp);
+// open (nullable): this launch opens the step; mlp: the learned guess (null:
+// acoustic)
 hipError_t launch_fiver(const IfaceArgs& a, bool record, const StepOpen* open, const MlpDev* mlp, hipStream_t s);
 hipError_t launch_phase(const PhaseArgs& a, hipStream_t s);
 // Batched forms: cmap lists the compaction chunks as (run, chunk of run); the

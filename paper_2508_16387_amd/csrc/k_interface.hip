@@ -23,7 +23,7 @@
 // launches of their own took 4.5 + 4.6 + 4.8 us of a 128^3 step that keeps its
 // queue, where the two now take 4.3 and 1 more in the first FIVER launch, and
 // 20.8 + 4.7 + 8.4 us, with 11.4 for that FIVER launch, where it is rebuilt:
-// 18.0 + 20.3 now.  General EOS, 128^3 charge, whose queue is rebuilt in every
+// 17.1 + 19.2 now.  General EOS, 128^3 charge, whose queue is rebuilt in every
 // step by a launch of its own: 25 + 5 + 10 -> 21 + 10 us.  The face -> slot
 // map is written only at the faces of the new queue and read only at faces
 // whose cells differ in material under the same frozen ids, so entries left
@@ -232,9 +232,9 @@ __device__ __forceinline__ int count_total(const IfaceArgs& a) { return count_pr
 __device__ __forceinline__ bool failed_before(int err) { return err != 0 && err != ST_RIEMANN_OPENING; }
 
 // An opening launch's error becomes an ordinary one, when that launch is over.
-__device__ __forceinline__ void settle_error(DevScalars* sc)
+__device__ __forceinline__ void settle_error(DevScalars* sc, int err)
 {
-    if (sc->err == ST_RIEMANN_OPENING) sc->err = ST_RIEMANN;
+    if (err == ST_RIEMANN_OPENING) sc->err = ST_RIEMANN;
 }
 
 // End of a step (single grid) that no kernel reported an error of: counters
@@ -292,8 +292,9 @@ __device__ __forceinline__ void open_step(const IfaceArgs& a, const StepOpen& o,
 
 __global__ void k_end_step(DevScalars* sc, int stages)
 {
-    if (sc->err == 0) end_step_body(sc, stages);
-    settle_error(sc);
+    const int err = sc->err;
+    if (err == 0) end_step_body(sc, stages);
+    settle_error(sc, err);
 }
 
 hipError_t launch_end_step(DevScalars* sc, int stages, hipStream_t s)
@@ -340,18 +341,28 @@ __device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int bas
             if (tot == 0) continue;                               // wave-uniform
             int o = off + incl - n;
             const int f0 = (int)(3u * (wbase + 256u * e + 4u * lane));
-            for (int q = 0; q < 12; ++q)
-                if (bits12 & (1u << q)) {
-                    if (!PART || (o >= from && o < to)) {
+            if (!PART || (off >= from && off + tot <= to)) {      // wave-uniform, as a rule true
+                for (int q = 0; q < 12; ++q)
+                    if (bits12 & (1u << q)) {
                         a.queue[o] = f0 + q;                      // 3 (c0 + b) + d = f0 + 3b + d
                         a.fslot[f0 + q] = o;
+                        ++o;
                     }
-                    ++o;
-                }
+            } else if (off < to && off + tot > from) {
+                for (int q = 0; q < 12; ++q)
+                    if (bits12 & (1u << q)) {
+                        if (o >= from && o < to) {
+                            a.queue[o] = f0 + q;
+                            a.fslot[f0 + q] = o;
+                        }
+                        ++o;
+                    }
+            }
             off += tot;
         }
         return total;
     }
+    const bool whole = !PART || (off >= from && off + cnt <= to);   // wave-uniform, as a rule true
     // byte path: faces in ascending id order: by cell, then by axis
     const uint64_t below = (1ull << lane) - 1ull;
     for (int e = 0; e < COMPACT_CELLS_PER_THREAD; ++e) {
@@ -363,7 +374,7 @@ __device__ __forceinline__ int scatter_body(const IfaceArgs& a, int blk, int bas
 #pragma unroll
         for (int d = 0; d < 3; ++d)
             if (bits & (1u << d)) {
-                if (!PART || (o >= from && o < to)) {
+                if (whole || (o >= from && o < to)) {
                     a.queue[o] = f0 + d;
                     a.fslot[f0 + d] = o;
                 }
@@ -393,78 +404,101 @@ __device__ __forceinline__ void scatter_chunk(const IfaceArgs& a, int chunk)
     }
 }
 
-// A rebuilt queue shared out over the launch that also solves it: units of at
-// most COMPACT_THREADS faces of one compaction block, in the order of the
-// queue.  (With a compaction block per launch block, whatever it holds, an
-// interface along a layer of the grid, all of whose faces lie in a few
-// compaction blocks, is few blocks' work: a flat surface across z beside a
-// moving bubble took 371 us per step at 128^3 and 172 at 64^3; 299 and 101
-// in units, 304 and 150 with the queue in launches of its own.)
-// Thread t looks after compaction blocks 2t and 2t + 1.
-constexpr int UNIT_BLOCKS = 2 * COMPACT_THREADS;
+// A rebuilt queue shared out over the launch that also solves it, in units of
+// at most COMPACT_THREADS faces of one compaction block.  Launch block b takes
+// the first unit of compaction block b, which as a rule holds all its faces;
+// the further units, where there are any, are numbered through and start at
+// the launch blocks without a compaction block.  (With a compaction block per
+// launch block, whatever it holds, an interface along a layer of the grid, all
+// of whose faces lie in a few compaction blocks, is few blocks' work: a flat
+// surface across z beside a moving bubble took 371 us per step at 128^3 and
+// 172 at 64^3; 300 and 100 in units, 304 and 150 with the queue in launches of
+// its own.  A launch block per unit in the order of the queue, every block
+// scanning the counts for its first one, took 1 us more of a launch where no
+// compaction block has a second unit, and 4 us at 50x43x37.)
+constexpr int UNIT_BLOCKS = 2 * COMPACT_THREADS;      // compaction blocks at most
 static_assert(UNIT_BLOCKS <= COMPACT_CHUNKS, "a count per compaction block");
-struct QueueUnits {
-    int cnt[2], face[2], unit[2];     // faces of the two, and the faces and units before them
-    int faces, units;                 // of the whole queue
+
+// Units after the first of a compaction block of cnt faces.
+__device__ __forceinline__ int further_units(int cnt) { return max(cnt - 1, 0) / COMPACT_THREADS; }
+
+struct QueueShare {
+    int base, cnt;                    // of the block's own compaction block: faces before it, and its faces
+    int faces, further;               // of the whole queue: faces, and further units
+    int c0, c1;                       // faces of compaction blocks 2t and 2t + 1, t the thread
 };
 
-__device__ __forceinline__ int units_of(int cnt) { return (cnt + COMPACT_THREADS - 1) / COMPACT_THREADS; }
+__device__ __forceinline__ QueueShare queue_share(const IfaceArgs& a, int blk)
+{
+    __shared__ int sS[3][COMPACT_THREADS / 64];
+    QueueShare u = {};
+    const int b0 = 2 * (int)threadIdx.x;
+    if (blk < a.nblk) u.cnt = a.blockcnt[blk];
+    if (b0 < a.nblk) u.c0 = a.blockcnt[b0];
+    if (b0 + 1 < a.nblk) u.c1 = a.blockcnt[b0 + 1];
+    u.faces = u.c0 + u.c1;
+    u.base = (b0 < blk ? u.c0 : 0) + (b0 + 1 < blk ? u.c1 : 0);
+    u.further = further_units(u.c0) + further_units(u.c1);
+    for (int o = 32; o > 0; o >>= 1) {
+        u.faces += __shfl_xor(u.faces, o);
+        u.base += __shfl_xor(u.base, o);
+        u.further += __shfl_xor(u.further, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sS[0][threadIdx.x >> 6] = u.faces;
+        sS[1][threadIdx.x >> 6] = u.base;
+        sS[2][threadIdx.x >> 6] = u.further;
+    }
+    __syncthreads();
+    u.faces = u.base = u.further = 0;
+    for (int k = 0; k < COMPACT_THREADS / 64; ++k) {
+        u.faces += sS[0][k];
+        u.base += sS[1][k];
+        u.further += sS[2][k];
+    }
+    return u;
+}
 
-__device__ __forceinline__ void queue_units(const IfaceArgs& a, QueueUnits& u)
+// Compaction block (x), its first queue position (y) and the positions [z, w)
+// of further unit n.
+__device__ __forceinline__ int4 find_unit(const QueueShare& qs, int n)
 {
     __shared__ int sF[COMPACT_THREADS / 64], sU[COMPACT_THREADS / 64];
+    __shared__ int4 sAt;
     const int b0 = 2 * (int)threadIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) u.cnt[k] = b0 + k < a.nblk ? a.blockcnt[b0 + k] : 0;
-    const int f = u.cnt[0] + u.cnt[1], n = units_of(u.cnt[0]) + units_of(u.cnt[1]);
-    int fi = f, ni = n;
+    const int c0 = qs.c0, c1 = qs.c1;
+    const int f = c0 + c1, u = further_units(c0) + further_units(c1);
+    int face = f, unit = u;
     for (int o = 1; o < 64; o <<= 1) {
-        const int x = __shfl_up(fi, o), y = __shfl_up(ni, o);
+        const int x = __shfl_up(face, o), y = __shfl_up(unit, o);
         if (lane >= o) {
-            fi += x;
-            ni += y;
+            face += x;
+            unit += y;
         }
     }
     if (lane == 63) {
-        sF[w] = fi;
-        sU[w] = ni;
+        sF[w] = face;
+        sU[w] = unit;
     }
     __syncthreads();
-    u.faces = u.units = 0;
-    u.face[0] = fi - f;
-    u.unit[0] = ni - n;
-    for (int k = 0; k < COMPACT_THREADS / 64; ++k) {
-        if (k < w) {
-            u.face[0] += sF[k];
-            u.unit[0] += sU[k];
-        }
-        u.faces += sF[k];
-        u.units += sU[k];
+    face -= f;
+    unit -= u;
+    for (int k = 0; k < w; ++k) {
+        face += sF[k];
+        unit += sU[k];
     }
-    u.face[1] = u.face[0] + u.cnt[0];
-    u.unit[1] = u.unit[0] + units_of(u.cnt[0]);
-}
-
-// Writes the queue entries of unit n of the queue, at positions [from, to),
-// for the block to read.
-__device__ __forceinline__ void scatter_unit(const IfaceArgs& a, const QueueUnits& u, int n, int& from, int& to)
-{
-    __shared__ int sBlk, sBase, sFrom, sTo;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int part = n - u.unit[k];
-        if (part >= 0 && part < units_of(u.cnt[k])) {             // one thread of the block
-            sBlk = 2 * (int)threadIdx.x + k;
-            sBase = u.face[k];
-            sFrom = u.face[k] + part * COMPACT_THREADS;
-            sTo = min(sFrom + COMPACT_THREADS, u.face[k] + u.cnt[k]);
+    int part = n - unit;
+    if (part >= 0 && part < u) {                                  // one thread of the block
+        const bool second = part >= further_units(c0);
+        if (second) {
+            part -= further_units(c0);
+            face += c0;
         }
+        const int from = face + (part + 1) * COMPACT_THREADS;
+        sAt = make_int4(b0 + (second ? 1 : 0), face, from, min(from + COMPACT_THREADS, face + (second ? c1 : c0)));
     }
     __syncthreads();
-    from = sFrom;
-    to = sTo;
-    scatter_body<true>(a, sBlk, sBase, from, to);
-    __syncthreads();                              // (also before the words above are written again)
+    return sAt;
 }
 
 // The queue alone, and the opening of the step: where FIVER does not do both
@@ -520,14 +554,15 @@ __device__ __forceinline__ void cell_prim(const Grid& G, const eos::EosK* sEos, 
 // F0, F1 (EG): families of materials 0 and 1 fixed at compile time, so that
 // a kernel carries the wave curves and EOS forms of those two families only
 // (-1: dispatched at run time).
-// open (nullable): the first launch of a step, which opens it and writes a
-// rebuilt queue: each block writes and solves units of it (queue_units; a
-// unit is seldom full, as the interface lies in the grid, which costs little
-// for stiffened gases, and saves a launch).
-template <bool EG, bool LG = false, int F0 = -1, int F1 = -1>
-__device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int blk, int nblk, const StepOpen* open,
-                                           const MlpDev* m = nullptr)
+// OPEN: the first launch of a step, which opens it (open) and writes a rebuilt
+// queue: each block writes and solves units of it (queue_share; a unit is
+// seldom full, as the interface lies in the grid, which costs little for
+// stiffened gases, and saves a launch).
+template <bool EG, bool LG = false, int F0 = -1, int F1 = -1, bool OPEN = false>
+__device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int blk, int nblk,
+                                           const MlpDev* m = nullptr, const StepOpen* open = nullptr)
 {
+    static_assert(!OPEN || (!EG && !LG), "stiffened gases and the acoustic start open steps");
     static_assert(!(EG && LG) || (F0 >= 0 && F1 >= 0), "the general-EOS learned start needs the families");
     __shared__ unsigned long long sCnt[3][4];
     __shared__ int sHead[2];
@@ -546,152 +581,165 @@ __device__ __forceinline__ void fiver_body(const IfaceArgs& a, int record, int b
     const int32_t ahead = q0 < a.qcap ? a.queue[q0] : 0;
     if (threadIdx.x == 0) {
         const int err = sc->err, qlen = sc->qlen, reuse = sc->qreuse;
-        sHead[0] = (open ? failed_before(err) : err != 0) ? 0 : (open && !reuse ? 1 : qlen);
-        sHead[1] = open && !reuse;
+        sHead[0] = (OPEN ? failed_before(err) : err != 0) ? 0 : (OPEN && !reuse ? 1 : qlen);
+        sHead[1] = OPEN && !reuse;
     }
     if (EG) geos_stage(G, sEos);
     else __syncthreads();
-    const bool rebuilt = open && sHead[1];
-    int n = sHead[0], unit = blk;
-    QueueUnits qu = {};
+    const bool rebuilt = OPEN && sHead[1];
+    const int n = sHead[0];
+    QueueShare qs = {};
     if (rebuilt) {                                                   // block-uniform
-        queue_units(a, qu);
+        qs = queue_share(a, blk);
         // (no face of a queue past its capacity is solved: the overflow is
         // the step's one error, whichever block is first)
-        if (n == 0 || qu.faces > a.qcap) qu.units = 0;
-        n = 0;
+        if (n == 0 || qs.faces > a.qcap) qs.cnt = qs.further = 0;
     }
-    if (open && blk == 0) open_step(a, *open, qu.faces);
+    if (OPEN && blk == 0) open_step(a, *open, qs.faces);
     long long iters = 0, fallbacks = 0, mlp_fb = 0;
     // A kept queue in one sweep of the launch, a rebuilt one unit by unit.
     // (Whole wavefronts of 64 faces and whole blocks first: a short queue
     // spread over more wavefronts at 8 faces each took longer: 128^3 charge
     // 87 -> 328 us, 50x43x37 9.5 -> 15.8 us.)
-    const int stride = (rebuilt ? 1 : nblk) * (int)blockDim.x, known = rebuilt ? -1 : q0;
-    int first = q0;
-    do {
-        if (rebuilt) {                                               // block-uniform
-            if (unit >= qu.units) break;
-            scatter_unit(a, qu, unit, first, n);
-            first += (int)threadIdx.x;
-            unit += nblk;
+    const int known = rebuilt ? -1 : q0;
+    // one queue entry per thread, the last wavefront's beyond the end not live
+    auto face = [&](int q, bool live) __attribute__((always_inline)) {
+        uint32_t c = 0, cn = 0;
+        int d = 0;
+        if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)(q == known ? ahead : a.queue[q]), c, cn, d);
+        const int xa = live ? a.chi[c] : 0, xb = live ? a.chi[cn] : 0;
+        double qa[5], qb[5];
+        cell_prim<EG, FS>(G, sEos, a.Win, c, xa, qa);
+        cell_prim<EG, FS>(G, sEos, a.Win, cn, xb, qb);
+        const int t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
+        const double ua = qa[1 + d], ub = qb[1 + d];
+        const double gA = pick(G.gamma, xa), pcA = pick(G.pc, xa), gB = pick(G.gamma, xb), pcB = pick(G.pc, xb);
+        double out[4];
+        bool used = false;
+        bool hg = false;
+        double gs = 0.0;
+        if constexpr (LG && !EG) {
+            const bool skip = !live || acoustic_suffices(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB);
+            if (__ballot(!skip) != 0ull) {                       // wave-uniform
+                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                double plo = 0.0, P = 1.0;
+                if (!skip) mlp_features(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, x, plo, P);
+                gs = guess64_mem(*m, x, plo, P, skip);
+                hg = !skip;
+            }
+            if (!live) return;
         }
-        // LG: wave-uniform trip count (q may pass n in the last pass)
-        const int qend = LG ? (n + 63) / 64 * 64 : n;
-        for (int q = first; q < qend; q += stride) {
-            const bool live = !LG || q < n;
-            uint32_t c = 0, cn = 0;
-            int d = 0;
-            if (live) face_cells(G.nx, G.ny, G.nz, (uint32_t)(q == known ? ahead : a.queue[q]), c, cn, d);
-            const int xa = live ? a.chi[c] : 0, xb = live ? a.chi[cn] : 0;
-            double qa[5], qb[5];
-            cell_prim<EG, FS>(G, sEos, a.Win, c, xa, qa);
-            cell_prim<EG, FS>(G, sEos, a.Win, cn, xb, qb);
-            const int t1 = 1 + (d + 1) % 3, t2 = 1 + (d + 2) % 3;
-            const double ua = qa[1 + d], ub = qb[1 + d];
-            const double gA = pick(G.gamma, xa), pcA = pick(G.pc, xa), gB = pick(G.gamma, xb), pcB = pick(G.pc, xb);
-            double out[4];
-            bool used = false;
-            bool hg = false;
-            double gs = 0.0;
-            if constexpr (LG && !EG) {
-                const bool skip = !live || acoustic_suffices(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB);
-                if (__ballot(!skip) != 0ull) {                       // wave-uniform
-                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                    double plo = 0.0, P = 1.0;
-                    if (!skip) mlp_features(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, x, plo, P);
-                    gs = guess64_mem(*m, x, plo, P, skip);
-                    hg = !skip;
-                }
-                if (!live) continue;
-            }
-            int it;
-            if constexpr (EG) {
-                // material 0 always on the left: where the lower cell holds
-                // material 1 the mirrored problem is solved (p* unchanged, u*
-                // negated, the star densities swapped), so that every lane of a
-                // wavefront runs the same families' code on each side
-                const bool flip = xa != 0;
-                const double in[6] = {flip ? qb[0] : qa[0], flip ? -ub : ua, flip ? qb[4] : qa[4],
-                                      flip ? qa[0] : qb[0], flip ? -ua : ub, flip ? qa[4] : qb[4]};
-                double o[4];
-                constexpr int S0 = eos::fam_set(F0), S1 = eos::fam_set(F1);
-                if constexpr (LG) {
-                    // learned start (the families take it, see learned_pair):
-                    // the network evaluated by whole wavefronts for the faces
-                    // away from equilibrium, then the judged outer iteration
-                    eos::Pair P;
-                    const bool ok = live && eos::pair_init<S0, S1>(sEos[0], sEos[1], in, P);
-                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                    double plo = 0.0, Pn = 1.0;
-                    const bool skip = !ok || eos_near_equilibrium(P) || !eos_features(P, F0, F1, x, plo, Pn);
-                    double g = __builtin_nan("");
-                    if (__ballot(!skip) != 0ull) g = guess64_mem(*m, x, plo, Pn, skip);      // wave-uniform
-                    if (!live) continue;
-                    it = 0;
-                    for (int k = 0; k < 4; ++k) o[k] = __builtin_nan("");
-                    if (ok) it = eos::pair_solve<S0, S1, 8>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
-                } else {
-                    it = eos::solve_pair<S0, S1, 8>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
-                }
-                out[0] = o[0];
-                out[1] = flip ? -o[1] : o[1];
-                out[2] = flip ? o[3] : o[2];
-                out[3] = flip ? o[2] : o[3];
+        int it;
+        if constexpr (EG) {
+            // material 0 always on the left: where the lower cell holds
+            // material 1 the mirrored problem is solved (p* unchanged, u*
+            // negated, the star densities swapped), so that every lane of a
+            // wavefront runs the same families' code on each side
+            const bool flip = xa != 0;
+            const double in[6] = {flip ? qb[0] : qa[0], flip ? -ub : ua, flip ? qb[4] : qa[4],
+                                  flip ? qa[0] : qb[0], flip ? -ua : ub, flip ? qa[4] : qb[4]};
+            double o[4];
+            constexpr int S0 = eos::fam_set(F0), S1 = eos::fam_set(F1);
+            if constexpr (LG) {
+                // learned start (the families take it, see learned_pair):
+                // the network evaluated by whole wavefronts for the faces
+                // away from equilibrium, then the judged outer iteration
+                eos::Pair P;
+                const bool ok = live && eos::pair_init<S0, S1>(sEos[0], sEos[1], in, P);
+                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                double plo = 0.0, Pn = 1.0;
+                const bool skip = !ok || eos_near_equilibrium(P) || !eos_features(P, F0, F1, x, plo, Pn);
+                double g = __builtin_nan("");
+                if (__ballot(!skip) != 0ull) g = guess64_mem(*m, x, plo, Pn, skip);      // wave-uniform
+                if (!live) return;
+                it = 0;
+                for (int k = 0; k < 4; ++k) o[k] = __builtin_nan("");
+                if (ok) it = eos::pair_solve<S0, S1, 8>(sEos[0], sEos[1], P, G.rtol, G.maxit, G.rds, g, o, &used);
             } else {
-                it = riemann_solve(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, G.rtol, G.maxit, hg, gs, out,
-                                   &used);
+                it = eos::solve_pair<S0, S1, 8>(sEos[0], sEos[1], in, G.rtol, G.maxit, G.rds, o);
             }
-            // faces that started from the acoustic guess (near equilibrium, or
-            // the judge preferred it)
-            mlp_fb += LG && !used && it != 0;
-            if (it == 0) {
-                report_error(&sc->err, &sc->err_cell, open ? ST_RIEMANN_OPENING : ST_RIEMANN, c);
-                continue;
-            }
-            iters += it < 0 ? -it : it;
-            fallbacks += it < 0;
-            const double ps = out[0], us = out[1];
-            double Fl[5], Fu[5];
-            if constexpr (EG) {
-                geos_flux<FS>(sEos[xa], G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, Fl);
-                geos_flux<FS>(sEos[xb], G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], Fu);
-            } else {
-                num_flux<double>(G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, gA, pcA,
-                                 pick(G.gpc, xa), pick(G.inv_gm1, xa), Fl);
-                num_flux<double>(G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], gB, pcB,
-                                 pick(G.gpc, xb), pick(G.inv_gm1, xb), Fu);
-            }
-            // face frame (mass, normal, t1, t2, energy) -> global components;
-            // the ten fluxes of a face are contiguous (one address per face for
-            // the stage kernel that reads them)
-            double* const fq = a.fluxF + 10 * (long long)q;
-            double fo[10];
-            fo[0] = Fl[0];
-            fo[1 + d] = Fl[1];
-            fo[t1] = Fl[2];
-            fo[t2] = Fl[3];
-            fo[4] = Fl[4];
-            fo[5] = Fu[0];
-            fo[6 + d] = Fu[1];
-            fo[5 + t1] = Fu[2];
-            fo[5 + t2] = Fu[3];
-            fo[9] = Fu[4];
+            out[0] = o[0];
+            out[1] = flip ? -o[1] : o[1];
+            out[2] = flip ? o[3] : o[2];
+            out[3] = flip ? o[2] : o[3];
+        } else {
+            it = riemann_solve(qa[0], ua, qa[4], gA, pcA, qb[0], ub, qb[4], gB, pcB, G.rtol, G.maxit, hg, gs, out,
+                               &used);
+        }
+        // faces that started from the acoustic guess (near equilibrium, or
+        // the judge preferred it)
+        mlp_fb += LG && !used && it != 0;
+        if (it == 0) {
+            report_error(&sc->err, &sc->err_cell, OPEN ? ST_RIEMANN_OPENING : ST_RIEMANN, c);
+            return;
+        }
+        iters += it < 0 ? -it : it;
+        fallbacks += it < 0;
+        const double ps = out[0], us = out[1];
+        double Fl[5], Fu[5];
+        if constexpr (EG) {
+            geos_flux<FS>(sEos[xa], G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, Fl);
+            geos_flux<FS>(sEos[xb], G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], Fu);
+        } else {
+            num_flux<double>(G.flux, qa[0], ua, qa[t1], qa[t2], qa[4], out[2], us, qa[t1], qa[t2], ps, gA, pcA,
+                             pick(G.gpc, xa), pick(G.inv_gm1, xa), Fl);
+            num_flux<double>(G.flux, out[3], us, qb[t1], qb[t2], ps, qb[0], ub, qb[t1], qb[t2], qb[4], gB, pcB,
+                             pick(G.gpc, xb), pick(G.inv_gm1, xb), Fu);
+        }
+        // face frame (mass, normal, t1, t2, energy) -> global components;
+        // the ten fluxes of a face are contiguous (one address per face for
+        // the stage kernel that reads them)
+        double* const fq = a.fluxF + 10 * (long long)q;
+        double fo[10];
+        fo[0] = Fl[0];
+        fo[1 + d] = Fl[1];
+        fo[t1] = Fl[2];
+        fo[t2] = Fl[3];
+        fo[4] = Fl[4];
+        fo[5] = Fu[0];
+        fo[6 + d] = Fu[1];
+        fo[5 + t1] = Fu[2];
+        fo[5 + t2] = Fu[3];
+        fo[9] = Fu[4];
 #pragma unroll
-            for (int v = 0; v < 10; ++v) fq[v] = fo[v];
-            if (record) {
-                const long long Q = a.qcap;
-                a.star[0 * Q + q] = ps;
-                a.star[1 * Q + q] = us;
-                a.star[2 * Q + q] = out[2];
-                a.star[3 * Q + q] = out[3];
-                a.star[4 * Q + q] = qa[t1];
-                a.star[5 * Q + q] = qa[t2];
-                a.star[6 * Q + q] = qb[t1];
-                a.star[7 * Q + q] = qb[t2];
-            }
+        for (int v = 0; v < 10; ++v) fq[v] = fo[v];
+        if (record) {
+            const long long Q = a.qcap;
+            a.star[0 * Q + q] = ps;
+            a.star[1 * Q + q] = us;
+            a.star[2 * Q + q] = out[2];
+            a.star[3 * Q + q] = out[3];
+            a.star[4 * Q + q] = qa[t1];
+            a.star[5 * Q + q] = qa[t2];
+            a.star[6 * Q + q] = qb[t1];
+            a.star[7 * Q + q] = qb[t2];
         }
-    } while (rebuilt);
+    };
+    if constexpr (OPEN) {
+        // (passes of a kept queue and units of a rebuilt one in one loop, so
+        // that the solve is there once)
+        int pass = rebuilt && blk < a.nblk && qs.cnt == 0 ? blk + nblk : blk;
+        // (the launch has a.nblk blocks or more)
+        // (block-uniform)
+        while (rebuilt ? pass < a.nblk || pass - a.nblk < qs.further : pass * COMPACT_THREADS < n) {
+            int from = pass * COMPACT_THREADS, to = n;
+            if (rebuilt) {
+                int4 at = make_int4(pass, qs.base, qs.base, qs.base + min(qs.cnt, COMPACT_THREADS));
+                if (pass >= a.nblk) at = find_unit(qs, pass - a.nblk);
+                from = at.z;
+                to = at.w;
+                scatter_body<true>(a, at.x, at.y, from, to);
+                __syncthreads();                                     // the block reads its own entries
+            }
+            const int q = from + (int)threadIdx.x;
+            if (q < to) face(q, true);
+            pass += nblk;
+        }
+    } else {
+        // LG: wave-uniform trip count (q may pass n in the last pass)
+        const int qend = LG ? (n + 63) / 64 * 64 : n, stride = nblk * (int)blockDim.x;
+        for (int q = q0; q < qend; q += stride) face(q, !LG || q < n);
+    }
     // counters: one atomic per block and counter (same-address atomics from
     // every wavefront serialise into a measurable tail)
     for (int o = 32; o > 0; o >>= 1) {
@@ -720,25 +768,25 @@ static_assert(COMPACT_THREADS == 256, "the FIVER kernels run compaction blocks")
 
 __global__ __launch_bounds__(256) void k_fiver(const IfaceArgs a, int record)
 {
-    fiver_body<false>(a, record, blockIdx.x, gridDim.x, nullptr);
+    fiver_body<false>(a, record, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void k_fiver_open(const IfaceArgs a, int record, const StepOpen o)
 {
-    fiver_body<false>(a, record, blockIdx.x, gridDim.x, &o);
+    fiver_body<false, false, -1, -1, true>(a, record, blockIdx.x, gridDim.x, nullptr, &o);
 }
 
 template <int F0, int F1>
 __global__ __launch_bounds__(256) void k_fiver_eos(const IfaceArgs a, int record)
 {
-    fiver_body<true, false, F0, F1>(a, record, blockIdx.x, gridDim.x, nullptr);
+    fiver_body<true, false, F0, F1>(a, record, blockIdx.x, gridDim.x);
 }
 
 // with the learned start, for the family pairs that take it (learned_pair)
 template <int F0, int F1>
 __global__ __launch_bounds__(256) void k_fiver_eos_learned(const IfaceArgs a, int record, const MlpDev m)
 {
-    fiver_body<true, true, F0, F1>(a, record, blockIdx.x, gridDim.x, nullptr, &m);
+    fiver_body<true, true, F0, F1>(a, record, blockIdx.x, gridDim.x, &m);
 }
 
 template <int F0, int F1>
@@ -761,7 +809,7 @@ static_assert(M2C_EOS_NASG == 0 && M2C_EOS_MG == 1 && M2C_EOS_JWL == 2, "family-
 
 __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int record, const MlpDev m)
 {
-    fiver_body<false, true>(a, record, blockIdx.x, gridDim.x, nullptr, &m);
+    fiver_body<false, true>(a, record, blockIdx.x, gridDim.x, &m);
 }
 
 // With a general EOS the queue is a launch of its own: a face takes so long
@@ -769,7 +817,7 @@ __global__ __launch_bounds__(256) void k_fiver_learned(const IfaceArgs a, int re
 // than the launch (128^3 charge, a compaction block to a launch block: FIVER 80
 // -> 131 us); with the learned guess too, whose network takes whole wavefronts
 // of faces; and on grids of more compaction blocks than a launch block looks
-// after counts (queue_units), where the queue is work, not latency (384^3, a
+// after counts (queue_share), where the queue is work, not latency (384^3, a
 // compaction block to a launch block: the first FIVER launch 64 us against 30,
 // of a 5 ms step).
 bool fiver_opens(const IfaceArgs& a, const MlpDev* mlp) { return !(a.g.eosg || mlp || a.nblk > UNIT_BLOCKS); }
@@ -943,10 +991,11 @@ hipError_t launch_phase(const PhaseArgs& a, hipStream_t s)
 template <bool EG>
 __global__ __launch_bounds__(COMPACT_THREADS) void k_step_begin(const IfaceArgs a, const PhaseArgs pa, int prev)
 {
+    const int err = a.sc->err;                    // (read beside the words of the decision)
     const bool kept = queue_kept(a.sc);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.sc->qreuse = kept ? 1 : 0;
-        settle_error(a.sc);                       // (stays an error to the blocks that read it meanwhile)
+        settle_error(a.sc, err);                  // (stays an error to the blocks that read it meanwhile)
     }
     if (kept) return;
     if (prev) phase_body<EG>(pa, blockIdx.x, gridDim.x);
@@ -1023,7 +1072,7 @@ hipError_t launch_compact_batch(const RunDesc* runs, const int2* cmap, int ncblo
 __global__ __launch_bounds__(64) void k_fiver_batch(const RunDesc* __restrict__ runs, int stage, int per_run)
 {
     const int r = blockIdx.x / per_run, b = blockIdx.x % per_run;
-    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, per_run, nullptr);
+    fiver_body<false>(iface_of_run(runs[r], stage), stage == 2, b, per_run);
 }
 
 // One-wavefront blocks, about 8192 over the batch (the solves
